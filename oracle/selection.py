@@ -271,32 +271,35 @@ def call_bytes(key) -> int:
     return 0
 
 
+def slot_grid(v: int, T: int, W: int) -> int:
+    """Row passes: a row is ceil(W / v) slots of v elements, one slot per
+    work-item, the slots of all rows numbered through."""
+    return min(cdiv(T * cdiv(W, v), BLOCK), GRID_CAP)
+
+
 def sw_role(dtype: int, I: int, flags: int, stream: bool, T: int) -> Tuple[int, int]:
     """Flat when aligned and contiguous (nontemporal when the call streams,
-    call_bytes > STREAM_BYTES, the same as the fused chain's role), vector
-    rows when only the rows are aligned, element-wise otherwise."""
+    call_bytes > STREAM_BYTES, the same as the fused chain's role), row slots
+    otherwise: aligned ones when the rows are aligned and whole vectors
+    long, element-aligned ones for any other rows."""
     v = 16 // elem_size(dtype)
     if (flags & ALIGN) and (flags & CONTIG):
         nvec = (T * I) // v
         return (SW_FLAT_NT if stream else SW_FLAT), max(1, min(cdiv(nvec, BLOCK), GRID_CAP))
-    if (flags & ALIGN) and I % v == 0:
-        cb = cdiv(I // v, BLOCK)
-        return SW_ROWS, min(T * cb, GRID_CAP)
-    return SW_SCALAR, min(cdiv(T * I, BLOCK), GRID_CAP)
+    return SW_ROWS if (flags & ALIGN) and I % v == 0 else SW_SCALAR, slot_grid(v, T, I)
 
 
 def elt_role(dtype: int, W: int, flags: int, b: int, T: int) -> Tuple[int, int]:
     """silu / add / masked_fill: flat vectors when aligned and contiguous
-    (beyond decode sizes two per work-item), vector rows when only the rows
-    are aligned, element-wise otherwise."""
+    (beyond decode sizes two per work-item), row slots otherwise: aligned
+    ones when the rows are aligned and whole vectors long, element-aligned
+    ones for any other rows."""
     v = 16 // elem_size(dtype)
     if (flags & ALIGN) and (flags & CONTIG):
         if b <= DECODE_BUCKET_MAX:
             return ELT_FLAT, max(1, min(cdiv((T * W) // v, BLOCK), GRID_CAP))
         return ELT_FLAT_U2, max(1, min(cdiv((T * W) // v, 2 * BLOCK), GRID_CAP))
-    if (flags & ALIGN) and W % v == 0:
-        return ELT_ROWS, min(T * cdiv(W // v, BLOCK), GRID_CAP)
-    return ELT_SCALAR, min(cdiv(T * W, BLOCK), GRID_CAP)
+    return ELT_ROWS if (flags & ALIGN) and W % v == 0 else ELT_SCALAR, slot_grid(v, T, W)
 
 
 def emb_role(dtype: int, H: int, flags: int, T: int) -> Tuple[int, int]:
@@ -911,9 +914,9 @@ def grid_of(variant: int, dt: int, T: int, width: int, slices: int = 1, tokens: 
     plain wide norm rows (res False): wide_grid; other norm and RoPE
     kernels: one workgroup per row or token (vector RoPE:
     times its slices, or per `tokens` tokens); flat kernels: one 16-byte vector per work-item (two
-    for ELT_FLAT_U2); row kernels: the row's vectors over 256 work-items,
-    per row; element-wise kernels: one element per work-item. Flat, row and
-    element-wise grids are capped at GRID_CAP (grid-stride beyond)."""
+    for ELT_FLAT_U2); row passes: one slot of a vector's elements per
+    work-item. Flat and row grids are capped at GRID_CAP (grid-stride
+    beyond)."""
     v = 16 // elem_size(dt)
     if variant in RN_WAVE.values():
         return cdiv(T, 4)
@@ -932,10 +935,8 @@ def grid_of(variant: int, dt: int, T: int, width: int, slices: int = 1, tokens: 
         return max(1, min(cdiv((T * width) // v, 2 * BLOCK), GRID_CAP))
     if variant in (EMB_VEC, EMB_SCALAR):
         return max(1, min(T, GRID_CAP))
-    if variant in (SW_ROWS, ELT_ROWS):
-        return min(T * cdiv(width // v, BLOCK), GRID_CAP)
-    if variant in (SW_SCALAR, ELT_SCALAR):
-        return min(cdiv(T * width, BLOCK), GRID_CAP)
+    if variant in (SW_ROWS, ELT_ROWS, SW_SCALAR, ELT_SCALAR):
+        return slot_grid(v, T, width)
     raise ValueError(variant)
 
 

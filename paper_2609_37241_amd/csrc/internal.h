@@ -117,7 +117,6 @@ Role sw_role(uint32_t dtype, int64_t I, unsigned flags, bool stream, int64_t T);
 // Bytes a call at the top of the key's token bucket moves (SwiGLU and the
 // chain; 0 for other ops); SwiGLU streams nontemporally above kStreamBytes.
 uint64_t call_bytes(const Key &k);
-constexpr uint64_t kStreamBytes = uint64_t(320) << 20;
 // Workgroups of a role variant for T tokens; `width` is the row width of
 // the launch's op (H for the norms, I for SwiGLU, W for the short ops); a
 // vector RoPE role takes T * slices workgroups with head slices, else

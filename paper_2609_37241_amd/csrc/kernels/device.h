@@ -1047,44 +1047,108 @@ __device__ __forceinline__ void sw_flat_part(const SwArgs &a, int64_t blk, int64
   }
 }
 
-// Aligned rows with padded strides: (row, 256-vector chunk) items.
-template <int DT>
-__device__ __forceinline__ void sw_rows_part(const SwArgs &a, int64_t blk, int64_t nblk) {
+// Row-wise passes over [T, W]: a row is ceil(W / V) slots of V elements (the
+// last one shorter when W is no whole number of vectors), and the slots of
+// all rows are numbered through, so every lane of a workgroup has one
+// whatever the row length. Rows that follow each other without a gap are one
+// row of T * W elements. A work-item finds its row by one division, of 32
+// bits unless there are more slots than that (a 64-bit division is about a
+// hundred instructions, as much as the rest of a SwiGLU vector).
+struct Slots {
+  int64_t T, W, per_row, total;
+};
+template <int V>
+__device__ __forceinline__ Slots make_slots(int64_t T, int64_t W, bool contiguous) {
+  Slots s;
+  s.T = contiguous ? 1 : T;
+  s.W = contiguous ? T * W : W;
+  s.per_row = (s.W + V - 1) / V;
+  s.total = s.T * s.per_row;
+  return s;
+}
+// Row and first element of slot `i`.
+template <int V>
+__device__ __forceinline__ void slot_at(const Slots &s, int64_t i, int64_t &row, int64_t &e0) {
+  if (s.T == 1) {
+    row = 0;
+    e0 = i * V;
+  } else if (s.total <= int64_t(0xFFFFFFFFu)) {
+    const uint32_t r = uint32_t(i) / uint32_t(s.per_row);
+    row = r;
+    e0 = int64_t(uint32_t(i) - r * uint32_t(s.per_row)) * V;
+  } else {
+    row = i / s.per_row;
+    e0 = (i - row * s.per_row) * V;
+  }
+}
+
+// 16-byte access at element e of a row: aligned, or at any element (ANY).
+template <int DT, bool ANY, bool NT>
+__device__ __forceinline__ u32x4 ld_slot(const void *row, int64_t e) {
+  using vec = typename Select<ANY, typename AnyVec<DT>::type, u32x4>::type;
+  const vec *p = reinterpret_cast<const vec *>(static_cast<const char *>(row) + e * Elt<DT>::ES);
+  if constexpr (NT)
+    return __builtin_nontemporal_load(p);
+  else
+    return *p;
+}
+template <int DT, bool ANY, bool NT>
+__device__ __forceinline__ void st_slot(void *row, int64_t e, const u32x4 &v) {
+  using vec = typename Select<ANY, typename AnyVec<DT>::type, u32x4>::type;
+  vec *p = reinterpret_cast<vec *>(static_cast<char *>(row) + e * Elt<DT>::ES);
+  if constexpr (NT)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
+}
+
+// Rows with padded strides: aligned and whole vectors long, or of any start
+// and length (ANY).
+template <int DT, bool ANY, bool NT>
+__device__ __forceinline__ void sw_slots(const SwArgs &a, int64_t blk, int64_t nblk) {
   using E = Elt<DT>;
   constexpr int V = E::V;
-  const int64_t nvr = a.I / V;
-  const int64_t cb = (nvr + kThreads - 1) / kThreads;
-  const int64_t total = a.T * cb;
-  for (int64_t it = blk; it < total; it += nblk) {
-    const int64_t row = it / cb;
-    const int64_t vi = (it - row * cb) * kThreads + threadIdx.x;
-    if (vi < nvr) {
-      const u32x4 gv = reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.gate) +
-                                                        row * a.g_rs * E::ES)[vi];
-      const u32x4 uv = reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.up) +
-                                                        row * a.u_rs * E::ES)[vi];
-      float fg[V], fu[V];
+  const Slots sl = make_slots<V>(a.T, a.I, ANY && a.g_rs == a.I && a.u_rs == a.I && a.o_rs == a.I);
+  for (int64_t i = blk * kThreads + threadIdx.x; i < sl.total; i += nblk * kThreads) {
+    int64_t row, e0;
+    slot_at<V>(sl, i, row, e0);
+    const char *g = static_cast<const char *>(a.gate) + row * a.g_rs * E::ES;
+    const char *u = static_cast<const char *>(a.up) + row * a.u_rs * E::ES;
+    char *o = static_cast<char *>(a.out) + row * a.o_rs * E::ES;
+    float fg[V], fu[V];
+    if (!ANY || e0 + V <= sl.W) {
+      const u32x4 gv = ld_slot<DT, ANY, NT>(g, e0), uv = ld_slot<DT, ANY, NT>(u, e0);
       E::unpack(gv, fg);
       E::unpack(uv, fu);
 #pragma unroll
       for (int e = 0; e < V; ++e) fg[e] = silu_mul(fg[e], fu[e]);
-      reinterpret_cast<u32x4 *>(static_cast<char *>(a.out) + row * a.o_rs * E::ES)[vi] =
-          E::pack(fg);
+      st_slot<DT, ANY, NT>(o, e0, E::pack(fg));
+    } else {
+      const int m = int(sl.W - e0);   // 1 .. V - 1
+#pragma unroll
+      for (int e = 0; e < V - 1; ++e) {
+        fg[e] = e < m ? E::ld(g, e0 + e) : 0.0f;
+        fu[e] = e < m ? E::ld(u, e0 + e) : 0.0f;
+      }
+#pragma unroll
+      for (int e = 0; e < V - 1; ++e)
+        if (e < m) E::st(o, e0 + e, silu_mul(fg[e], fu[e]));
     }
   }
 }
 
-// Any alignment: element-wise over T*I.
-template <int DT>
-__device__ __forceinline__ void sw_scalar_part(const SwArgs &a, int64_t blk, int64_t nblk) {
-  using E = Elt<DT>;
-  const int64_t n = a.T * a.I;
-  for (int64_t e = blk * kThreads + threadIdx.x; e < n; e += nblk * kThreads) {
-    const int64_t row = e / a.I;
-    const int64_t j = e - row * a.I;
-    const float r = silu_mul(E::ld(a.gate, row * a.g_rs + j), E::ld(a.up, row * a.u_rs + j));
-    E::st(a.out, row * a.o_rs + j, r);
-  }
+// As the flat form, calls that move more than the last-level cache stream
+// nontemporally (a 2-read, 1-write stream of 1.2 GB over three buffer sets:
+// 6.52 against 5.98 TB/s). Bound by memory: bf16 4096 x 14336 on the halves
+// of a fused buffer 55.8 us (6.3 TB/s), against 61.0 us cached with a 64-bit
+// division per 256-vector piece of a row; 512 x 11008 one element off a
+// 16-byte boundary 6.5 against 13.6 us element by element.
+template <int DT, bool ANY>
+__device__ __forceinline__ void sw_rows_part(const SwArgs &a, int64_t blk, int64_t nblk) {
+  if (3 * a.n * Elt<DT>::ES > int64_t(kStreamBytes))
+    sw_slots<DT, ANY, true>(a, blk, nblk);
+  else
+    sw_slots<DT, ANY, false>(a, blk, nblk);
 }
 
 // ---- element-wise ops (silu, add, masked_fill) and embedding -------------------------
@@ -1127,33 +1191,49 @@ __device__ __forceinline__ uint32_t fill_bits(float value) {
     return Elt<kBF16>::pack2(value, 0.0f) & 0xFFFFu;   // round to nearest even
 }
 
-// The V mask bytes of vector vi of a row starting at `m` (aligned to V).
-template <int DT>
-__device__ __forceinline__ uint64_t mask_bytes(const uint8_t *m, int64_t vi) {
+// The V mask bytes of elements e .. e + V - 1 of a row starting at `m`, as
+// one load (aligned to V, or at any byte with ANY).
+template <int DT, bool ANY>
+__device__ __forceinline__ uint64_t mask_bytes(const uint8_t *m, int64_t e) {
+  typedef uint32_t u32b __attribute__((aligned(1)));
+  typedef uint64_t u64b __attribute__((aligned(1)));
   if constexpr (DT == kF32)
-    return reinterpret_cast<const uint32_t *>(m)[vi];
+    return *reinterpret_cast<const typename Select<ANY, u32b, uint32_t>::type *>(m + e);
   else
-    return reinterpret_cast<const uint64_t *>(m)[vi];
+    return *reinterpret_cast<const typename Select<ANY, u64b, uint64_t>::type *>(m + e);
 }
 
-template <int DT, int OP>
-__device__ __forceinline__ u32x4 elt_vector(u32x4 x, const void *b, int64_t vi,
-                                            const uint8_t *mrow, uint32_t fill, bool nt) {
+// The V elements x at element e of a row of an element-wise op; b is the
+// second operand's or the mask's row.
+template <int DT, int OP, bool ANY, bool NT>
+__device__ __forceinline__ u32x4 elt_vector(u32x4 x, const void *b, int64_t e, uint32_t fill) {
   using E = Elt<DT>;
   constexpr int V = E::V;
   if constexpr (OP == kOpMaskedFill) {
-    return mask_select<DT>(x, mask_bytes<DT>(mrow, vi), fill);
+    return mask_select<DT>(x, mask_bytes<DT, ANY>(static_cast<const uint8_t *>(b), e), fill);
   } else {
     float fa[V], fb[V];
     E::unpack(x, fa);
-    if constexpr (OP == kOpAdd) {
-      const u32x4 y = nt ? ld16<true>(static_cast<const u32x4 *>(b) + vi)
-                         : ld16<false>(static_cast<const u32x4 *>(b) + vi);
-      E::unpack(y, fb);
-    }
+    if constexpr (OP == kOpAdd) E::unpack(ld_slot<DT, ANY, NT>(b, e), fb);
 #pragma unroll
-    for (int e = 0; e < V; ++e) fa[e] = elt_value<OP>(fa[e], OP == kOpAdd ? fb[e] : 0.0f);
+    for (int i = 0; i < V; ++i) fa[i] = elt_value<OP>(fa[i], OP == kOpAdd ? fb[i] : 0.0f);
     return E::pack(fa);
+  }
+}
+
+// Element e of a row (masked_fill copies bit patterns).
+template <int DT, int OP>
+__device__ __forceinline__ void elt_element(const void *x, const void *b, void *o, int64_t e,
+                                            uint32_t fill) {
+  using E = Elt<DT>;
+  if constexpr (OP == kOpMaskedFill) {
+    const bool set = static_cast<const uint8_t *>(b)[e] != 0;
+    if constexpr (DT == kF32)
+      static_cast<uint32_t *>(o)[e] = set ? fill : static_cast<const uint32_t *>(x)[e];
+    else
+      static_cast<uint16_t *>(o)[e] = set ? uint16_t(fill) : static_cast<const uint16_t *>(x)[e];
+  } else {
+    E::st(o, e, elt_value<OP>(E::ld(x, e), OP == kOpAdd ? E::ld(b, e) : 0.0f));
   }
 }
 
@@ -1165,7 +1245,6 @@ __device__ __forceinline__ void elt_flat_part(const EltArgs &a, int64_t blk, int
   constexpr int V = E::V;
   const u32x4 *x = static_cast<const u32x4 *>(a.a);
   u32x4 *o = static_cast<u32x4 *>(a.out);
-  const uint8_t *m = static_cast<const uint8_t *>(a.b);
   const uint32_t fill = fill_bits<DT>(a.value);
   const int64_t step = nblk * kThreads * U;
   for (int64_t base = blk * kThreads * U + threadIdx.x; base < a.nvec; base += step) {
@@ -1178,67 +1257,40 @@ __device__ __forceinline__ void elt_flat_part(const EltArgs &a, int64_t blk, int
 #pragma unroll
     for (int k = 0; k < U; ++k) {
       const int64_t i = base + int64_t(k) * kThreads;
-      if (i < a.nvec) st16<NT>(o + i, elt_vector<DT, OP>(xv[k], a.b, i, m, fill, NT));
+      if (i < a.nvec) st16<NT>(o + i, elt_vector<DT, OP, false, NT>(xv[k], a.b, i * V, fill));
     }
   }
   if (blk == 0) {
     const int64_t i = a.nvec * V + threadIdx.x;
-    if (i < a.n) {
-      if constexpr (OP == kOpMaskedFill) {
-        if (m[i]) E::st(a.out, i, a.value);   // st rounds to the dtype
-        else E::st(a.out, i, E::ld(a.a, i));
-      } else {
-        E::st(a.out, i, elt_value<OP>(E::ld(a.a, i), OP == kOpAdd ? E::ld(a.b, i) : 0.0f));
-      }
-    }
+    if (i < a.n) elt_element<DT, OP>(a.a, a.b, a.out, i, fill);
   }
 }
 
-// Aligned rows with padded strides: (row, 256-vector chunk) items.
-template <int DT, int OP>
+// Rows with padded strides: aligned and whole vectors long, or of any start
+// and length (ANY). Bound by memory: masked_fill of bf16 8008 x 1001 takes
+// 7.6 us (5.3 TB/s, a contiguous Python call), against 19.7 us element by
+// element with a 64-bit division each.
+template <int DT, int OP, bool ANY>
 __device__ __forceinline__ void elt_rows_part(const EltArgs &a, int64_t blk, int64_t nblk) {
   using E = Elt<DT>;
   constexpr int V = E::V;
-  const int64_t nvr = a.W / V;
-  const int64_t cb = (nvr + kThreads - 1) / kThreads;
+  constexpr int BS = OP == kOpMaskedFill ? 1 : E::ES;
   const uint32_t fill = fill_bits<DT>(a.value);
-  for (int64_t it = blk; it < a.T * cb; it += nblk) {
-    const int64_t row = it / cb;
-    const int64_t vi = (it - row * cb) * kThreads + threadIdx.x;
-    if (vi < nvr) {
-      const u32x4 *x = reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.a) +
-                                                       row * a.a_rs * E::ES);
-      const char *brow = static_cast<const char *>(a.b) +
-                         row * a.b_rs * (OP == kOpMaskedFill ? 1 : E::ES);
-      u32x4 *o = reinterpret_cast<u32x4 *>(static_cast<char *>(a.out) + row * a.o_rs * E::ES);
-      o[vi] = elt_vector<DT, OP>(x[vi], brow, vi, reinterpret_cast<const uint8_t *>(brow), fill,
-                                 false);
-    }
-  }
-}
-
-// Any alignment: element-wise over T*W (masked_fill copies bit patterns).
-template <int DT, int OP>
-__device__ __forceinline__ void elt_scalar_part(const EltArgs &a, int64_t blk, int64_t nblk) {
-  using E = Elt<DT>;
-  const int64_t n = a.T * a.W;
-  for (int64_t e = blk * kThreads + threadIdx.x; e < n; e += nblk * kThreads) {
-    const int64_t row = e / a.W;
-    const int64_t j = e - row * a.W;
-    if constexpr (OP == kOpMaskedFill) {
-      const bool set = static_cast<const uint8_t *>(a.b)[row * a.b_rs + j] != 0;
-      if constexpr (DT == kF32) {
-        const uint32_t x = static_cast<const uint32_t *>(a.a)[row * a.a_rs + j];
-        static_cast<uint32_t *>(a.out)[row * a.o_rs + j] = set ? fill_bits<DT>(a.value) : x;
-      } else {
-        const uint16_t x = static_cast<const uint16_t *>(a.a)[row * a.a_rs + j];
-        static_cast<uint16_t *>(a.out)[row * a.o_rs + j] =
-            set ? uint16_t(fill_bits<DT>(a.value)) : x;
-      }
+  const Slots sl = make_slots<V>(a.T, a.W, ANY && a.a_rs == a.W && a.b_rs == a.W && a.o_rs == a.W);
+  for (int64_t i = blk * kThreads + threadIdx.x; i < sl.total; i += nblk * kThreads) {
+    int64_t row, e0;
+    slot_at<V>(sl, i, row, e0);
+    const char *x = static_cast<const char *>(a.a) + row * a.a_rs * E::ES;
+    const char *b = static_cast<const char *>(a.b) + row * a.b_rs * BS;
+    char *o = static_cast<char *>(a.out) + row * a.o_rs * E::ES;
+    if (!ANY || e0 + V <= sl.W) {
+      const u32x4 xv = ld_slot<DT, ANY, false>(x, e0);
+      st_slot<DT, ANY, false>(o, e0, elt_vector<DT, OP, ANY, false>(xv, b, e0, fill));
     } else {
-      const float r = elt_value<OP>(E::ld(a.a, row * a.a_rs + j),
-                                    OP == kOpAdd ? E::ld(a.b, row * a.b_rs + j) : 0.0f);
-      E::st(a.out, row * a.o_rs + j, r);
+      const int m = int(sl.W - e0);   // 1 .. V - 1
+#pragma unroll
+      for (int e = 0; e < V - 1; ++e)
+        if (e < m) elt_element<DT, OP>(x, b, o, e0 + e, fill);
     }
   }
 }
@@ -1539,12 +1591,12 @@ __device__ __forceinline__ void body_sw_flat(const SwArgs &a, uint32_t nblk = gr
 
 template <int DT>
 __device__ __forceinline__ void body_sw_rows(const SwArgs &a, uint32_t nblk = gridDim.x) {
-  sw_rows_part<DT>(a, blockIdx.x, nblk);
+  sw_rows_part<DT, false>(a, blockIdx.x, nblk);
 }
 
 template <int DT>
 __device__ __forceinline__ void body_sw_scalar(const SwArgs &a, uint32_t nblk = gridDim.x) {
-  sw_scalar_part<DT>(a, blockIdx.x, nblk);
+  sw_rows_part<DT, true>(a, blockIdx.x, nblk);
 }
 
 // U vectors per work-item, cached loads and stores.
@@ -1555,12 +1607,12 @@ __device__ __forceinline__ void body_elt_flat(const EltArgs &a, uint32_t nblk = 
 
 template <int DT, int OP>
 __device__ __forceinline__ void body_elt_rows(const EltArgs &a, uint32_t nblk = gridDim.x) {
-  elt_rows_part<DT, OP>(a, blockIdx.x, nblk);
+  elt_rows_part<DT, OP, false>(a, blockIdx.x, nblk);
 }
 
 template <int DT, int OP>
 __device__ __forceinline__ void body_elt_scalar(const EltArgs &a, uint32_t nblk = gridDim.x) {
-  elt_scalar_part<DT, OP>(a, blockIdx.x, nblk);
+  elt_rows_part<DT, OP, true>(a, blockIdx.x, nblk);
 }
 
 template <int DT, bool VEC>

@@ -83,7 +83,7 @@ bool split_fits(uint32_t dtype, int64_t H, uint32_t bucket) {
 // rows, back to back and after a 1 GiB read flush) put the split ahead
 // only for rows of 8192 vectors (by up to 15 % at 1-64 rows, where four
 // workgroups per row pull it from HBM in parallel). Unaligned or ragged
-// rows take the scalar kernel.
+// rows take RN_SCALAR, a workgroup per row with element-aligned vectors.
 Role rn_role(uint32_t dtype, int64_t H, unsigned flags, int64_t T, uint32_t bucket, bool res) {
   const int64_t v = vec_elems(dtype);
   if (!(flags & kAlign) || H % v) return {RN_SCALAR, uint32_t(T)};
@@ -164,6 +164,13 @@ uint64_t call_bytes(const Key &k) {
   return 0;
 }
 
+// Row passes (rows with padded strides, and rows of any start and length):
+// one slot of a vector's elements per work-item, the rows' slots numbered
+// through.
+uint32_t slot_grid(uint32_t dtype, int64_t T, int64_t W) {
+  return clamp_grid(cdiv(T * cdiv(W, vec_elems(dtype)), kBlock));
+}
+
 // Flat SwiGLU, one vector per work-item, standalone and as the fused
 // chain's role, streams nontemporally when the call moves more than
 // kStreamBytes: below that the operands stay in the 256 MiB last-level
@@ -177,13 +184,7 @@ Role sw_role(uint32_t dtype, int64_t I, unsigned flags, bool stream, int64_t T) 
     const int64_t nvec = (T * I) / v;
     return {stream ? SW_FLAT_NT : SW_FLAT, clamp_grid(cdiv(nvec, kBlock))};
   }
-  if ((flags & kAlign) && I % v == 0) {
-    const int64_t cb = cdiv(I / v, kBlock);
-    const int64_t g = T * cb;
-    return {SW_ROWS, g > int64_t(kGridCap) ? kGridCap : uint32_t(g)};
-  }
-  const int64_t g = cdiv(T * I, kBlock);
-  return {SW_SCALAR, g > int64_t(kGridCap) ? kGridCap : uint32_t(g)};
+  return {(flags & kAlign) && I % v == 0 ? SW_ROWS : SW_SCALAR, slot_grid(dtype, T, I)};
 }
 
 // Element-wise ops: flat vectors when aligned and contiguous (beyond decode
@@ -197,12 +198,7 @@ Role elt_role(uint32_t dtype, int64_t W, unsigned flags, uint32_t bucket, int64_
     if (bucket <= kDecodeBucketMax) return {ELT_FLAT, clamp_grid(cdiv((T * W) / v, kBlock))};
     return {ELT_FLAT_U2, clamp_grid(cdiv((T * W) / v, 2 * int64_t(kBlock)))};
   }
-  if ((flags & kAlign) && W % v == 0) {
-    const int64_t g = T * cdiv(W / v, kBlock);
-    return {ELT_ROWS, g > int64_t(kGridCap) ? kGridCap : uint32_t(g)};
-  }
-  const int64_t g = cdiv(T * W, kBlock);
-  return {ELT_SCALAR, g > int64_t(kGridCap) ? kGridCap : uint32_t(g)};
+  return {(flags & kAlign) && W % v == 0 ? ELT_ROWS : ELT_SCALAR, slot_grid(dtype, T, W)};
 }
 
 // Embedding: one workgroup per output row (grid-stride beyond the cap);
@@ -232,14 +228,8 @@ uint32_t role_grid(int32_t variant, uint32_t dtype, int64_t T, int64_t I, int32_
       return clamp_grid(cdiv((T * I) / vec_elems(dtype), 2 * int64_t(kBlock)));
     case EMB_VEC: case EMB_SCALAR:
       return clamp_grid(T);
-    case SW_ROWS: case ELT_ROWS: {
-      const int64_t g = T * cdiv(I / vec_elems(dtype), kBlock);
-      return g > int64_t(kGridCap) ? kGridCap : uint32_t(g);
-    }
-    case SW_SCALAR: case ELT_SCALAR: {
-      const int64_t g = cdiv(T * I, kBlock);
-      return g > int64_t(kGridCap) ? kGridCap : uint32_t(g);
-    }
+    case SW_ROWS: case ELT_ROWS: case SW_SCALAR: case ELT_SCALAR:
+      return slot_grid(dtype, T, I);
     default:
       return 0;
   }

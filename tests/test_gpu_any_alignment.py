@@ -92,3 +92,67 @@ def test_norm_rows(cache, dtype, H, res):
     check("y", host(yd), wy, dtype)
     untouched(yd, ybuf)
     assert cache.last_selection().variant == S.RN_SCALAR
+
+
+# Row passes of SwiGLU and the element-wise ops: widths below a vector, whole
+# vectors and tails of one and of V - 1 elements, rows that end inside a
+# workgroup, one row of several workgroups; gaps between rows (or none), and
+# operands at different distances from a boundary.
+def _slot_cases():
+    for dtype, v in ((nm.F32, 4), (nm.BF16, 8)):
+        for T, W in ((1, 1), (5, v - 1), (7, v), (3, v + 1), (9, 31 * v + v - 1), (4, 256 * v),
+                     (3, 257 * v + 1), (2, 1025 * v - 1)):
+            for off, pad in ((0, 0), (1, 0), (1, 3), (0, v)):
+                yield dtype, T, W, off, pad
+
+
+@pytest.mark.parametrize("op", ["swiglu", "silu", "add", "masked_fill"])
+@pytest.mark.parametrize("dtype,T,W,off,pad", list(_slot_cases()))
+def test_row_passes(cache, op, dtype, T, W, off, pad):
+    r = rng(T * 31 + W + off + pad)
+    a = wl.host_array(r, (T, W), dtype, outliers=True)
+    b = wl.host_array(r, (T, W), dtype)
+    ad, _ = put(a, dtype, off, pad)
+    bd, _ = put(b, dtype, 3 * off, 2 * pad)
+    od, obuf = put(np.zeros_like(a), dtype, 2 * off, pad)
+    if op == "swiglu":
+        cache.swiglu(ad, bd, out=od)
+        want = O.swiglu(a, b, dtype)
+    elif op == "silu":
+        cache.silu(ad, out=od)
+        want = O.silu(a, dtype)
+    elif op == "add":
+        cache.add(ad, bd, out=od)
+        want = O.add(a, b, dtype)
+    else:
+        mask = (r.random((T, W)) < 0.4).astype(np.uint8) * np.uint8(129)
+        mbuf = torch.zeros(off + T * (W + pad), dtype=torch.uint8, device=DEV)
+        md = torch.as_strided(mbuf, (T, W), (W + pad, 1), off)
+        md.copy_(torch.from_numpy(mask))
+        cache.masked_fill(ad, md, float("-inf"), out=od)
+        want = O.masked_fill(a, mask, float("-inf"), dtype)
+    exact = op in ("add", "masked_fill")
+    check(op, host(od), want, dtype, exact=exact)
+    untouched(od, obuf)
+    if op == "swiglu":                       # in place on the gate
+        cache.swiglu(ad, bd, out=ad)
+        check("in place", host(ad), want, dtype)
+
+
+@pytest.mark.parametrize("dtype,T,I", [(nm.BF16, 3000, 19008), (nm.BF16, 3001, 19009),
+                                       (nm.F32, 1500, 19001)])
+def test_streaming_swiglu_row_passes(cache, dtype, T, I):
+    """Calls of more than 320 MiB (nontemporal accesses), gate and up as the
+    halves of one buffer: sampled rows against the oracle, and every row
+    against calls of 500 rows (cached accesses), bit for bit."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(T)
+    td = torch.bfloat16 if dtype == nm.BF16 else torch.float32
+    gu = torch.randn((T, 2 * I), generator=g, device=DEV).to(td)
+    gate, up = gu[:, :I], gu[:, I:]
+    out = cache.swiglu(gate, up)
+    for lo in range(0, T, 500):
+        part = cache.swiglu(gate[lo:lo + 500], up[lo:lo + 500])
+        assert torch.equal(out[lo:lo + 500], part), lo
+    rows = torch.tensor([0, 1, T // 2, T - 1], device=DEV)
+    check("rows", host(out[rows]), O.swiglu(host(gate[rows]), host(up[rows]), dtype), dtype)
