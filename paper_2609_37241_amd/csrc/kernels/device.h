@@ -882,82 +882,210 @@ __device__ __forceinline__ void rope_vec_block(const RopeArgs &a, int64_t blk, f
   }
 }
 
-// Any alignment / head size / variant: one token per workgroup, element
-// pairs. `lds` holds 2 * 256 floats (cos, sin), and 256 more for QKN. Pairs
-// are (i, i + rd/2), or (2i, 2i + 1) with kRopeInterleaved.
-//
-// QKN: heads are taken 256 at a time; wavefront w reduces the squares of
-// heads w, w + 4, ... of the slice (element-wise loads, any alignment) and
-// leaves 1/rms in LDS, then all work-items normalise and rotate the slice,
-// and normalise the elements past rd.
-template <int DT, bool QKN = false>
-__device__ __forceinline__ void rope_scalar_block(const RopeArgs &a, int64_t t, float *lds) {
+// m elements (whole vectors: m >= V) at element e of a head that starts at any
+// element; zeros past them.
+template <int DT>
+__device__ __forceinline__ u32x4 ld_part(const char *head, int e, int m) {
   using E = Elt<DT>;
+  const char *p = head + e * E::ES;
+  if (m >= E::V) return *reinterpret_cast<const typename AnyVec<DT>::type *>(p);
+  float f[E::V];
+#pragma unroll
+  for (int i = 0; i < E::V; ++i) f[i] = i < m ? E::ld(p, i) : 0.0f;
+  return E::pack(f);   // exact: the floats came from elements
+}
+template <int DT>
+__device__ __forceinline__ void st_part(char *head, int e, int m, const float *f) {
+  using E = Elt<DT>;
+  char *p = head + e * E::ES;
+  if (m >= E::V) {
+    *reinterpret_cast<typename AnyVec<DT>::type *>(p) = E::pack(f);
+  } else {
+#pragma unroll
+    for (int i = 0; i < E::V - 1; ++i)
+      if (i < m) E::st(p, i, f[i]);
+  }
+}
+
+// Any alignment, head size and variant: one token per workgroup, `lds` holds
+// 2 * 256 floats (cos, sin). As in rope_vec_block a group of lanes takes a
+// head, one chunk of V elements each (of both halves, rotate-half; of V / 2
+// adjacent pairs, INTER), but the chunks of a head need not be a power of
+// two, whole or aligned: a group is the next power of two of lanes, of which
+// the last ones may have no chunk, the last chunk may be short, and accesses
+// are element-aligned. PF heads per group are requested before the angle
+// math and the barrier.
+//
+// QKN: the group sums the squares of its head, so a group is at most 64
+// lanes; chunks beyond that (float32, INTER, more than 256 elements) and the
+// elements past rd, which are normalised only, are read again after the sum.
+//
+// Bound by memory latency and the lanes that a group leaves idle: 2048
+// tokens of 64 heads of 96 (bf16, six of eight lanes) take 10.0 us (5.1 TB/s),
+// against 14.8 us with one element pair per work-item and a division each;
+// 512 tokens of 64 heads of 128 one element off a 16-byte boundary 5.5 us,
+// against 10.3 us.
+template <int DT, bool QKN, bool INTER, int PF = 2>
+__device__ __forceinline__ void rope_any_block(const RopeArgs &a, int64_t t, float *lds) {
+  using E = Elt<DT>;
+  constexpr int V = E::V;
   const int P2 = a.rd >> 1;
-  const bool inter = a.mode & kRopeInterleaved;
-  float *cs = lds;
-  float *sn = lds + 256;
-  for (int i = threadIdx.x; i < P2; i += kThreads) {
-    float c, s;
-    rope_cos_sin(a, t, i, c, s);
-    cs[i] = c;
-    sn[i] = s;
+  const int span = INTER ? a.rd : P2;
+  const int cpb = (span + V - 1) / V;
+  int lg = cpb > 1 ? 32 - __builtin_clz(unsigned(cpb - 1)) : 0;
+  if (QKN && lg > 6) lg = 6;
+  const int G = 1 << lg;
+  const int lane = int(threadIdx.x) & (G - 1);
+  const int hg = int(threadIdx.x) >> lg, hstep = kThreads >> lg;
+  const int nh = a.nq + a.nk;
+  const int e0 = lane * V;
+  const int m = span - e0;               // elements of this lane's chunk (idle: <= 0)
+  const int pass = QKN ? a.hd - a.rd : 0;
+  float *cs = lds, *sn = lds + 256;
+
+  // the angle operands of pair threadIdx.x, ahead of the heads
+  const bool ang = int(threadIdx.x) < P2;
+  float c = 1.0f, s = 0.0f;
+  int64_t pos = 0;
+  if (ang) {
+    pos = rope_pos(a, t);
+    if (a.mode & kRopeCache) {
+      const int64_t r = pos < 0 ? 0 : (pos >= a.cs_len ? a.cs_len - 1 : pos);
+      const float *row = a.cos_sin + r * a.rd;
+      c = row[threadIdx.x];
+      s = row[P2 + threadIdx.x];
+    } else {
+      c = a.inv_freq[threadIdx.x];
+    }
+  }
+
+  u32x4 wq1, wq2, wk1, wk2;
+  if constexpr (QKN) {
+    const char *qw = static_cast<const char *>(a.qw);
+    const char *kw = a.kw ? static_cast<const char *>(a.kw) : qw;
+    if (m > 0) {
+      wq1 = ld_part<DT>(qw, e0, m);
+      wk1 = ld_part<DT>(kw, e0, m);
+      if constexpr (!INTER) {
+        wq2 = ld_part<DT>(qw, P2 + e0, m);
+        wk2 = ld_part<DT>(kw, P2 + e0, m);
+      }
+    }
+  }
+
+  u32x4 x1[PF], x2[PF];
+  auto gather = [&](int h) {
+#pragma unroll
+    for (int j = 0; j < PF; ++j) {
+      x1[j] = x2[j] = u32x4{0, 0, 0, 0};
+      if (m > 0 && h + j * hstep < nh) {
+        const char *b = rope_head(a, t, h + j * hstep, E::ES);
+        x1[j] = ld_part<DT>(b, e0, m);
+        if constexpr (!INTER) x2[j] = ld_part<DT>(b, P2 + e0, m);
+      }
+    }
+  };
+  gather(hg);
+
+  if (ang) {
+    if (!(a.mode & kRopeCache)) {
+      const float inv = c;
+      sincosf(float(pos) * inv, &s, &c);
+    }
+    cs[threadIdx.x] = c;
+    sn[threadIdx.x] = s;
   }
   __syncthreads();
-  const int nh = a.nq + a.nk;
-  if constexpr (!QKN) {
-    const int total = nh * P2;
-    for (int e = threadIdx.x; e < total; e += kThreads) {
-      const int h = e / P2;
-      const int i = e - h * P2;
-      const int i0 = inter ? 2 * i : i, i1 = inter ? 2 * i + 1 : i + P2;
-      char *base = rope_head(a, t, h, E::ES);
-      const float v1 = E::ld(base, i0), v2 = E::ld(base, i1);
-      E::st(base, i0, rot_a(v1, v2, cs[i], sn[i]));
-      E::st(base, i1, rot_b(v1, v2, cs[i], sn[i]));
+
+  // normalise (QKN) and rotate the chunk at element e of the span
+  auto rotate = [&](char *b, int e, int n, float *f1, float *f2, float inv, const u32x4 &w1,
+                    const u32x4 &w2) {
+    if constexpr (QKN) {
+      float w[V];
+      E::unpack(w1, w);
+#pragma unroll
+      for (int i = 0; i < V; ++i) f1[i] = (f1[i] * inv) * w[i];
+      if constexpr (!INTER) {
+        E::unpack(w2, w);
+#pragma unroll
+        for (int i = 0; i < V; ++i) f2[i] = (f2[i] * inv) * w[i];
+      }
     }
-  } else {
-    float *rinv = lds + 512;
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const void *kw = a.kw ? a.kw : a.qw;
-    const int pass = a.hd - a.rd;
-    for (int h0 = 0; h0 < nh; h0 += kThreads) {
-      const int hn = nh - h0 < kThreads ? nh - h0 : kThreads;
-      for (int hl = wid; hl < hn; hl += kThreads / 64) {
-        const char *base = rope_head(a, t, h0 + hl, E::ES);
+    float o1[V], o2[V];
+    if constexpr (INTER) {
+#pragma unroll
+      for (int i = 0; i < V; i += 2) {
+        const float ci = cs[(e + i) >> 1], si = sn[(e + i) >> 1];
+        o1[i] = rot_a(f1[i], f1[i + 1], ci, si);
+        o1[i + 1] = rot_b(f1[i], f1[i + 1], ci, si);
+      }
+      st_part<DT>(b, e, n, o1);
+    } else {
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        const float ci = cs[e + i], si = sn[e + i];
+        o1[i] = rot_a(f1[i], f2[i], ci, si);
+        o2[i] = rot_b(f1[i], f2[i], ci, si);
+      }
+      st_part<DT>(b, e, n, o1);
+      st_part<DT>(b, P2 + e, n, o2);
+    }
+  };
+
+  for (int h0 = hg; h0 < nh; h0 += PF * hstep) {
+    if (h0 != hg) gather(h0);
+#pragma unroll
+    for (int j = 0; j < PF; ++j) {
+      const int h = h0 + j * hstep;
+      if (h >= nh) continue;              // uniform over a group
+      char *b = rope_head(a, t, h, E::ES);
+      float f1[V], f2[V];
+      E::unpack(x1[j], f1);
+      E::unpack(x2[j], f2);
+      float inv = 1.0f;
+      const char *hw = nullptr;
+      if constexpr (QKN) {
+        hw = static_cast<const char *>(h < a.nq || !a.kw ? a.qw : a.kw);
         float ss = 0.0f;
-        for (int i = lane; i < a.hd; i += 64) {
-          const float v = E::ld(base, i);
-          ss = __builtin_fmaf(v, v, ss);
+#pragma unroll
+        for (int i = 0; i < V; ++i) ss = __builtin_fmaf(f1[i], f1[i], ss);
+        if constexpr (!INTER) {
+#pragma unroll
+          for (int i = 0; i < V; ++i) ss = __builtin_fmaf(f2[i], f2[i], ss);
         }
-        ss = wave_sum(ss);
-        if (lane == 0) rinv[hl] = rsqrtf(ss / float(a.hd) + a.eps);
+        auto add = [&](int e, int n) {
+          float f[V];
+          E::unpack(ld_part<DT>(b, e, n), f);
+#pragma unroll
+          for (int i = 0; i < V; ++i) ss = __builtin_fmaf(f[i], f[i], ss);
+        };
+        if constexpr (INTER)
+          for (int e = e0 + G * V; e < span; e += G * V) add(e, span - e);
+        for (int e = e0; e < pass; e += G * V) add(a.rd + e, pass - e);
+        ss = group_sum(ss, G);
+        inv = rsqrtf(ss / float(a.hd) + a.eps);
       }
-      __syncthreads();
-      const int total = hn * P2;
-      for (int e = threadIdx.x; e < total; e += kThreads) {
-        const int hl = e / P2;
-        const int i = e - hl * P2;
-        const int i0 = inter ? 2 * i : i, i1 = inter ? 2 * i + 1 : i + P2;
-        const int h = h0 + hl;
-        const void *w = h < a.nq ? a.qw : kw;
-        char *base = rope_head(a, t, h, E::ES);
-        const float r = rinv[hl];
-        const float n1 = (E::ld(base, i0) * r) * E::ld(w, i0);
-        const float n2 = (E::ld(base, i1) * r) * E::ld(w, i1);
-        E::st(base, i0, rot_a(n1, n2, cs[i], sn[i]));
-        E::st(base, i1, rot_b(n1, n2, cs[i], sn[i]));
+      if (m > 0) {
+        const bool isq = h < a.nq;
+        rotate(b, e0, m, f1, f2, inv, QKN && isq ? wq1 : wk1, QKN && isq ? wq2 : wk2);
       }
-      const int tp = hn * pass;
-      for (int e = threadIdx.x; e < tp; e += kThreads) {
-        const int hl = e / pass;
-        const int j = a.rd + (e - hl * pass);
-        const int h = h0 + hl;
-        const void *w = h < a.nq ? a.qw : kw;
-        char *base = rope_head(a, t, h, E::ES);
-        E::st(base, j, (E::ld(base, j) * rinv[hl]) * E::ld(w, j));
+      if constexpr (QKN) {
+        if constexpr (INTER) {
+          for (int e = e0 + G * V; e < span; e += G * V) {
+            const u32x4 w1 = ld_part<DT>(hw, e, span - e);
+            E::unpack(ld_part<DT>(b, e, span - e), f1);
+            rotate(b, e, span - e, f1, f2, inv, w1, w1);
+          }
+        }
+        for (int e = e0; e < pass; e += G * V) {
+          float w[V];
+          E::unpack(ld_part<DT>(b, a.rd + e, pass - e), f1);
+          E::unpack(ld_part<DT>(hw, a.rd + e, pass - e), w);
+#pragma unroll
+          for (int i = 0; i < V; ++i) f1[i] = (f1[i] * inv) * w[i];
+          st_part<DT>(b, a.rd + e, pass - e, f1);
+        }
       }
-      __syncthreads();
     }
   }
 }
@@ -1576,8 +1704,11 @@ __device__ __forceinline__ void body_rope_vec(const RopeArgs &a) {
 
 template <int DT, bool QKN>
 __device__ __forceinline__ void body_rope_scalar(const RopeArgs &a) {
-  __shared__ float lds[(QKN ? 3 : 2) * 256];
-  rope_scalar_block<DT, QKN>(a, blockIdx.x, lds);
+  __shared__ float lds[2 * 256];
+  if (a.mode & kRopeInterleaved)
+    rope_any_block<DT, QKN, true>(a, blockIdx.x, lds);
+  else
+    rope_any_block<DT, QKN, false>(a, blockIdx.x, lds);
 }
 
 // The bodies that stride over the grid take the launch's workgroup count:

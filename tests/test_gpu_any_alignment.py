@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-@pytest.fixture(scope="module")
+@pytest.fixture
 def cache():
     import paper_2609_37241_amd as tri
     c = tri.SpecCache()
@@ -156,3 +156,44 @@ def test_streaming_swiglu_row_passes(cache, dtype, T, I):
         assert torch.equal(out[lo:lo + 500], part), lo
     rows = torch.tensor([0, 1, T // 2, T - 1], device=DEV)
     check("rows", host(out[rows]), O.swiglu(host(gate[rows]), host(up[rows]), dtype), dtype)
+
+
+# RoPE heads of any size and start: halves (or pairs) of one short chunk, of
+# whole chunks that are no power of two, with a short last chunk; more heads
+# than one pass of a workgroup; partial rotary spans; the largest head, where
+# a float32 head of pairs has more chunks than a wavefront has lanes.
+def _rope_cases():
+    for hd, rd in ((2, 0), (6, 0), (18, 0), (80, 0), (96, 0), (96, 34), (120, 0), (192, 0),
+                   (256, 40), (510, 0), (512, 0)):
+        for nq, nk in ((1, 0), (5, 2), (33, 9)):
+            yield hd, rd, nq, nk
+
+
+@pytest.mark.parametrize("qkn", [False, True], ids=["plain", "qkn"])
+@pytest.mark.parametrize("inter", [False, True], ids=["half", "pairs"])
+@pytest.mark.parametrize("dtype", [nm.F32, nm.BF16])
+@pytest.mark.parametrize("hd,rd,nq,nk", list(_rope_cases()))
+def test_rope_heads(cache, dtype, hd, rd, nq, nk, inter, qkn):
+    import paper_2609_37241_amd as tri
+    r = rng(hd * 7 + rd + nq)
+    T, span = 3, rd or hd
+    q, k = wl.host_array(r, (T, nq, hd), dtype), wl.host_array(r, (T, nk, hd), dtype)
+    qw, kw = wl.host_weight(r, hd, dtype), wl.host_weight(r, hd, dtype)
+    table = wl.cos_sin_table(r, 64, span) if hd % 4 else None
+    pos = r.integers(-2, 70, size=T).astype(np.int64)
+    tt = torch.from_numpy(table).to(DEV) if table is not None else None
+    ext = tri.rope_ext(rotary_dim=rd, interleaved=inter, pos_int64=True, cos_sin=tt)
+    for off, pad in ((0, 0), (1, 3)):
+        qd, qbuf = put(q, dtype, off, pad)
+        kd, kbuf = put(k, dtype, 2 * off, pad) if nk else (None, None)
+        qwd = put(qw[None], dtype, off, 0)[0][0] if qkn else None
+        kwd = put(kw[None], dtype, off, 0)[0][0] if qkn and nk else None
+        cache.rope(qd, kd, torch.from_numpy(pos).to(DEV), 1e4, ext, q_w=qwd, k_w=kwd)
+        wq, wk = O.rope_ext(q, k, pos, 1e4, dtype, q_w=qw if qkn else None,
+                            k_w=kw if qkn else None, eps=1e-6, rotary_dim=span, interleaved=inter,
+                            cos_sin=table)
+        check("q", host(qd), wq, dtype)
+        untouched(qd, qbuf)
+        if nk:
+            check("k", host(kd), wk, dtype)
+            untouched(kd, kbuf)
