@@ -9,7 +9,12 @@ the missed key and calls again -- the paper's miss path (Sec. 3.5), with
 "compile" replaced by selecting a precompiled kernel variant.
 
 PyTorch is used for device memory and streams only. There is no fallback:
-if libtri.so is missing, importing this package raises.
+if libtri.so or _fast.so is missing, importing this package raises.
+
+The op methods first hand their arguments to the native form of the same
+call (csrc/binding/fast.cpp), which takes plain tensors on the cache's
+device and returns None for everything else; the Python code after it then
+makes the checks, raises the errors and records prepared calls.
 """
 from __future__ import annotations
 
@@ -28,6 +33,11 @@ __all__ = ["SpecCache", "Graph", "TriError", "dtype_code", "rope_ext", "Selectio
            "E_NOMEM", "E_LAUNCH", "E_RUNTIME", "F32", "BF16", "AUTO_INSTALL"]
 
 _dll = L.load()
+try:
+    from . import _fast     # after libtri.so, which it shares
+except ImportError as e:
+    raise ImportError("the binding's extension module _fast.so is missing or does not load: "
+                      "build it first (python -c 'import __graft_entry__ as g; g.build()')") from e
 
 
 class TriError(RuntimeError):
@@ -36,6 +46,8 @@ class TriError(RuntimeError):
         name = _dll.tri_status_str(status).decode()
         super().__init__(f"{what}: {name} ({status})" if what else f"{name} ({status})")
 
+
+_fast.setup(TriError, RopeExt, ChainArgs)
 
 _DT = {torch.float32: F32, torch.bfloat16: BF16}
 
@@ -238,6 +250,8 @@ class Prepared:
 class SpecCache:
     """One native specialization cache (bound to the current device)."""
 
+    _fast = None      # the native op calls (set with the handle)
+
     def __init__(self, capacity: int = 0, auto_install: bool = False, jit: bool = False,
                  code_dir: Optional[str] = None, autotune: bool = False,
                  generic: bool = False, resident_args: bool = False):
@@ -260,6 +274,7 @@ class SpecCache:
             raise TriError(st, "tri_spec_cache_create")
         self._h = h
         self._dev = torch.cuda.current_device()   # the device the cache is bound to
+        self._fast = _fast.Handle(h.value, self._dev)
         self.misses_handled = 0
         self._rec = None                           # prepare(): the recorded entry call
         if code_dir is not None:
@@ -269,6 +284,8 @@ class SpecCache:
 
     def close(self):
         if self._h:
+            if self._fast is not None:
+                self._fast.close()
             _dll.tri_spec_cache_destroy(self._h)
             self._h = None
 
@@ -294,11 +311,14 @@ class SpecCache:
         for _ in range(max_misses):
             if st != MISS:
                 break
-            self.install_last_miss()
-            self.misses_handled += 1
+            self._on_miss()
             st = fn(self._h, *args)
         if st != OK:
             raise TriError(st, what)
+
+    def _on_miss(self) -> None:
+        self.install_last_miss()
+        self.misses_handled += 1
 
     def prepare(self, op: str, *args, **kwargs) -> Prepared:
         """Marshal one call of method `op` (e.g. "rmsnorm", "swiglu",
@@ -331,6 +351,10 @@ class SpecCache:
     # ---- ops ---------------------------------------------------------------
     def rmsnorm(self, x: torch.Tensor, w: torch.Tensor, eps: float = 1e-6,
                 out: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
+        if self._rec is None:
+            r = self._fast.rmsnorm(self, x, w, eps, out, stream)
+            if r is not None:
+                return r
         T, H = _dims(x, "x", 2, self._dev)
         y = torch.empty_like(x) if out is None else out
         _like(y, "out", x.shape, x.dtype, self._dev)
@@ -342,6 +366,10 @@ class SpecCache:
 
     def residual_rmsnorm(self, x, residual, w, eps: float = 1e-6, out=None, residual_out=None,
                          stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
+        if self._rec is None:
+            r = self._fast.residual_rmsnorm(self, x, residual, w, eps, out, residual_out, stream)
+            if r is not None:
+                return r
         T, H = _dims(x, "x", 2, self._dev)
         _like(residual, "residual", x.shape, x.dtype, self._dev)
         y = torch.empty_like(x) if out is None else out
@@ -398,6 +426,10 @@ class SpecCache:
 
     def rope_qk(self, q, k, pos, base: float = 10000.0, stream=None):
         """In-place RoPE of q [T, nq, hd] and k [T, nk, hd] (k may be None)."""
+        if self._rec is None:
+            r = self._fast.rope(self, q, k, pos, base, None, None, None, 0.0, stream, 0)
+            if r is not None:
+                return r
         T, nq, nk, hd, kp, kts = self._qk(q, k, pos, torch.int32)
         self._call("tri_rope_qk", _dll.tri_rope_qk, dtype_code(q.dtype), q.data_ptr(),
                    _tokens(q, "q", nq, hd), kp, kts, pos.data_ptr(), T, nq, nk, hd, base,
@@ -408,6 +440,10 @@ class SpecCache:
                      stream=None):
         """In-place per-head RMSNorm (weights q_w / k_w [hd]) then RoPE of
         q [T, nq, hd] and k [T, nk, hd] (k may be None)."""
+        if self._rec is None:
+            r = self._fast.rope(self, q, k, pos, base, None, q_w, k_w, eps, stream, 1)
+            if r is not None:
+                return r
         T, nq, nk, hd, kp, kts = self._qk(q, k, pos, torch.int32)
         _vector(q_w, "q_w", hd, q.dtype, self._dev)
         if k_w is not None:
@@ -423,6 +459,10 @@ class SpecCache:
         """In-place RoPE of q [T, nq, hd] and k [T, nk, hd] (k may be None)
         with an optional variant (`rope_ext(...)`) and, with q_w, the per-head
         QK RMSNorm first (tri_rope_qk_ext)."""
+        if self._rec is None:
+            r = self._fast.rope(self, q, k, pos, base, ext, q_w, k_w, eps, stream, 2)
+            if r is not None:
+                return r
         pos_dt = torch.int64 if ext is not None and ext.pos_int64 else torch.int32
         T, nq, nk, hd, kp, kts = self._qk(q, k, pos, pos_dt)
         _check_cos_sin(ext, hd, self._dev)
@@ -438,6 +478,10 @@ class SpecCache:
         return q, k
 
     def swiglu(self, gate, up, out=None, stream=None) -> torch.Tensor:
+        if self._rec is None:
+            r = self._fast.swiglu(self, gate, up, out, stream)
+            if r is not None:
+                return r
         T, I = _dims(gate, "gate", 2, self._dev)
         _like(up, "up", gate.shape, gate.dtype, self._dev)
         o = torch.empty_like(gate) if out is None else out
@@ -450,6 +494,10 @@ class SpecCache:
     # ---- short ops ---------------------------------------------------------------
     def silu(self, x, out=None, stream=None) -> torch.Tensor:
         """out = x / (1 + exp(-x)) over [T, W]."""
+        if self._rec is None:
+            r = self._fast.silu(self, x, out, stream)
+            if r is not None:
+                return r
         T, W = _dims(x, "x", 2, self._dev)
         o = torch.empty_like(x) if out is None else out
         _like(o, "out", x.shape, x.dtype, self._dev)
@@ -460,6 +508,10 @@ class SpecCache:
 
     def add(self, a, b, out=None, stream=None) -> torch.Tensor:
         """out = a + b over [T, W] (one rounding)."""
+        if self._rec is None:
+            r = self._fast.add(self, a, b, out, stream)
+            if r is not None:
+                return r
         T, W = _dims(a, "a", 2, self._dev)
         _like(b, "b", a.shape, a.dtype, self._dev)
         o = torch.empty_like(a) if out is None else out
@@ -471,6 +523,10 @@ class SpecCache:
 
     def masked_fill(self, x, mask, value: float, out=None, stream=None) -> torch.Tensor:
         """out = where(mask, value, x); mask is uint8 (or bool) [T, W]."""
+        if self._rec is None:
+            r = self._fast.masked_fill(self, x, mask, value, out, stream)
+            if r is not None:
+                return r
         if mask.dtype not in (torch.uint8, torch.bool):
             raise TypeError("mask must be uint8 or bool")
         T, W = _dims(x, "x", 2, self._dev)
@@ -486,6 +542,10 @@ class SpecCache:
 
     def embedding(self, table, ids, out=None, stream=None) -> torch.Tensor:
         """out[t] = table[ids[t]] (zeros for ids out of range); ids int32 / int64."""
+        if self._rec is None:
+            r = self._fast.embedding(self, table, ids, out, stream)
+            if r is not None:
+                return r
         if ids.dtype not in (torch.int32, torch.int64) or ids.dim() != 1:
             raise TypeError("ids must be a 1-D int32 or int64 tensor")
         n_rows, H = _dims(table, "table", 2, self._dev)
@@ -559,12 +619,16 @@ class SpecCache:
         return a, (y, ro, o)
 
     def decode_chain_args(self, args: ChainArgs, stream=None) -> None:
+        if self._rec is None and self._fast.chain(self, args, stream):
+            return
         self._call("tri_decode_chain", _dll.tri_decode_chain, C.byref(args),
                    _stream_ptr(stream, self._dev))
 
     def decode_chain_layers(self, layers, stream=None) -> None:
         """Several chains (a list of ChainArgs from chain_args) in one entry
         call, launched in list order (tri_decode_chain_layers)."""
+        if self._rec is None and self._fast.layers(self, layers, stream):
+            return
         arr = (ChainArgs * max(1, len(layers)))(*layers)
         self._call("tri_decode_chain_layers", _dll.tri_decode_chain_layers, arr, len(layers),
                    _stream_ptr(stream, self._dev), max_misses=len(layers))

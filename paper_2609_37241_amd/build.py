@@ -8,10 +8,12 @@ another launch backend (the CPU tests use a recording one).
 from __future__ import annotations
 
 import concurrent.futures as cf
+import importlib.util
 import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from typing import List, Optional
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -21,6 +23,7 @@ KDIR = os.path.join(CSRC, "kernels")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libtri.so")
+FAST_LIB = os.path.join(PKG, "_fast.so")
 BENCH_LIB = os.path.join(PKG, "libtri_bench.so")
 HOSTCOST_LIB = os.path.join(PKG, "libtri_hostcost.so")
 ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
@@ -89,6 +92,23 @@ def _obj(src: str) -> str:
     return os.path.join(BUILD, os.path.basename(src) + ".o")
 
 
+def torch_dir() -> str:
+    """The installed torch package's folder, found without importing it."""
+    return importlib.util.find_spec("torch").submodule_search_locations[0]
+
+
+def fast_compile_cmd() -> List[str]:
+    """The binding's native op calls (csrc/binding/fast.cpp) against the
+    installed torch and Python headers."""
+    inc = os.path.join(torch_dir(), "include")
+    src = os.path.join(CSRC, "binding", "fast.cpp")
+    system = [inc, os.path.join(inc, "torch", "csrc", "api", "include"),
+              os.path.join(ROCM, "include"), sysconfig.get_paths()["include"]]
+    flags = [f for d in system for f in ("-isystem", d)]
+    return [CXX, *HOST_FLAGS, "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__", *flags, "-c", src, "-o",
+            _obj(src)]
+
+
 def hip_sources() -> List[str]:
     return sorted(os.path.join(KDIR, f) for f in os.listdir(KDIR) if f.endswith(".hip"))
 
@@ -108,8 +128,9 @@ def build(jobs: Optional[int] = None) -> str:
     src = os.path.join(CSRC, HIP_BACKEND)
     cmds.append([CXX, *HOST_FLAGS, "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROCM, "include"),
                  "-c", src, "-o", _obj(src)])
+    fast = fast_compile_cmd()
     with cf.ThreadPoolExecutor(jobs) as ex:
-        for f in [ex.submit(_run, c) for c in cmds]:
+        for f in [ex.submit(_run, c) for c in [fast, *cmds]]:
             f.result()
     objs = [c[-1] for c in cmds]
     rocm_lib = os.path.join(ROCM, "lib")
@@ -117,6 +138,13 @@ def build(jobs: Optional[int] = None) -> str:
     _run([CXX, "-shared", "-o", tmp, *objs, "-L", rocm_lib, "-lamdhip64", "-lhiprtc",
           "-Wl,-soname,libtri.so", f"-Wl,-rpath,{rocm_lib}", "-Wl,--no-undefined"])
     shutil.move(tmp, LIB)
+    # the binding's extension module: libtri.so beside it, torch's libraries
+    # as the process has loaded them
+    torch_lib = os.path.join(torch_dir(), "lib")
+    tmp = FAST_LIB + ".tmp"
+    _run([CXX, "-shared", "-o", tmp, fast[-1], "-L", PKG, "-ltri", "-L", torch_lib,
+          "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"])
+    shutil.move(tmp, FAST_LIB)
     # the benchmark's native timing loops, linked against libtri.so
     # and a reference streaming copy (the practical HBM ceiling)
     harness = os.path.join(CSRC, "bench", "harness.cpp")

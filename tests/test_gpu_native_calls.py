@@ -1,0 +1,151 @@
+"""The op methods' native form (the binding's extension module) against the
+Python form of the same call, which a torch function mode selects: equal
+results, outputs placed as asked, one miss handled each, the same selection
+record; and the calls that the native form leaves to the Python checks. Each
+case also runs once on a side stream."""
+import pytest
+import torch
+from torch.overrides import TorchFunctionMode
+
+DEV = "cuda:0"
+
+
+class PythonForm(TorchFunctionMode):
+    def __torch_function__(self, func, types, args=(), kwargs=None):
+        return func(*args, **(kwargs or {}))
+
+
+def test_native_form_declines_what_is_not_plain():
+    """CPU tensors, wrong counts of arguments and other types: None, before
+    any native call (the handle's address is never used)."""
+    from paper_2609_37241_amd import _fast
+    h = _fast.Handle(0x1000, 0)
+    x, w = torch.zeros(2, 8), torch.ones(8)
+    assert h.rmsnorm(None, x, w, 1e-6, None, None) is None
+    assert h.rmsnorm(None, "x", w, 1e-6, None, None) is None
+    assert h.silu(None, x, None, None) is None
+    assert h.silu(None, x) is None
+    assert h.chain(None, object(), None) is None
+    assert h.layers(None, (), None) is None
+    h.close()
+    assert h.rmsnorm(None, x, w, 1e-6, None, None) is None
+
+
+@pytest.fixture(scope="module")
+def tri():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    import paper_2609_37241_amd as tri
+    return tri
+
+
+def _calls(tri):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(5)
+
+    def t(*shape, dt=torch.bfloat16):
+        return torch.randn(shape, generator=g, device=DEV).to(dt)
+
+    w, hw = torch.nn.Parameter(t(264)), t(128)
+    pos, pos64 = torch.arange(5, device=DEV, dtype=torch.int32), torch.arange(5, device=DEV)
+    wide = t(5, 600)
+    ext = tri.rope_ext(rotary_dim=64, pos_int64=True,
+                       cos_sin=t(9, 64, dt=torch.float32))
+    f = torch.float32
+    return {
+        "rmsnorm": lambda c, **k: c.rmsnorm(wide[:, :264], w, 1e-5, **k),
+        "rmsnorm_f32_out": lambda c, **k: c.rmsnorm(t(5, 264, dt=f), t(264, dt=f), 0,
+                                                    out=torch.empty(5, 264, device=DEV), **k),
+        "residual": lambda c, **k: c.residual_rmsnorm(wide[:, :264], t(5, 264), w, **k),
+        "swiglu": lambda c, **k: c.swiglu(wide[:, :300], wide[:, 300:], **k),
+        "silu": lambda c, **k: c.silu(wide, **k),
+        "add": lambda c, **k: c.add(t(1, 7), t(1, 7), **k),
+        "masked_fill": lambda c, **k: c.masked_fill(wide, wide > 0, float("-inf"), **k),
+        "embedding": lambda c, **k: c.embedding(wide, torch.tensor([4, 0, 7, -1], device=DEV), **k),
+        "rope_qk": lambda c, **k: c.rope_qk(t(5, 4, 128), t(5, 2, 128), pos, 1e4, **k),
+        "rope_no_k": lambda c, **k: c.rope_qk(t(5, 4, 128), None, pos, **k)[:1],
+        "qk_norm_rope": lambda c, **k: c.qk_norm_rope(t(5, 4, 128), t(5, 2, 128), pos, hw, hw, **k),
+        "rope_ext": lambda c, **k: c.rope(t(5, 4, 128), t(5, 2, 128), pos64, ext=ext, **k),
+        "empty": lambda c, **k: c.silu(wide[:0], **k),
+    }
+
+
+NAMES = ["rmsnorm", "rmsnorm_f32_out", "residual", "swiglu", "silu", "add", "masked_fill",
+         "embedding", "rope_qk", "rope_no_k", "qk_norm_rope", "rope_ext", "empty"]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", NAMES)
+def test_native_form_equals_the_python_form(tri, name):
+    got = []
+    for mode in (None, PythonForm, "stream"):
+        call, c = _calls(tri)[name], tri.SpecCache()       # the same draws each time
+        if mode is PythonForm:
+            with PythonForm():
+                r = call(c)
+        elif mode == "stream":
+            torch.cuda.synchronize()
+            s = torch.cuda.Stream()
+            r = call(c, stream=s)
+            s.synchronize()
+        else:
+            r = call(c)
+        torch.cuda.synchronize()
+        got.append((r if isinstance(r, tuple) else (r,), c.last_selection().as_tuple(), c.stats(),
+                    c.misses_handled))
+        c.close()
+    (native, sel, stats, misses), python, side = got
+    assert misses == (0 if name == "empty" else 1)
+    for other in (python, side):
+        assert (sel, stats, misses) == other[1:]
+        assert len(native) == len(other[0])
+        for a, b in zip(native, other[0]):
+            assert a.dtype == b.dtype and a.shape == b.shape and a.stride() == b.stride()
+            assert torch.equal(a, b)
+
+
+@pytest.mark.gpu
+def test_native_form_leaves_errors_to_the_python_checks(tri):
+    c = tri.SpecCache()
+    x, w = torch.zeros(3, 64, device=DEV), torch.ones(64, device=DEV)
+    for call, err in ((lambda: c.rmsnorm(x.half(), w.half()), TypeError),
+                      (lambda: c.rmsnorm(x, w.cpu()), ValueError),
+                      (lambda: c.rmsnorm(x[0], w), ValueError),
+                      (lambda: c.rmsnorm(x, w[:32]), ValueError),
+                      (lambda: c.silu(x.t()), ValueError),
+                      (lambda: c.silu(x, out=torch.empty(3, 32, device=DEV)), ValueError),
+                      (lambda: c.embedding(x, torch.zeros(2, device=DEV)), TypeError),
+                      (lambda: c.rope_qk(torch.zeros(3, 2, 32, device=DEV), None,
+                                         torch.zeros(3, device=DEV)), TypeError)):
+        with pytest.raises(err):
+            call()
+    assert c.stats()["calls"] == 0
+    with pytest.raises(tri.TriError) as e:
+        c.rmsnorm(x, w, -1.0)
+    assert e.value.status == tri.E_INVALID and "tri_rmsnorm" in str(e.value)
+    assert c.stats()["calls"] == 1
+    c.close()
+    with pytest.raises(tri.TriError):
+        c.rmsnorm(x, w)
+
+
+@pytest.mark.gpu
+def test_native_form_under_vmap_and_capture(tri):
+    """A batched tensor has no address of its own: refused, as by the Python
+    form. A call captured into a graph replays on new data."""
+    c = tri.SpecCache()
+    x = torch.randn(4, 256, device=DEV)
+    with pytest.raises(Exception):
+        torch.vmap(c.silu)(torch.randn(2, 3, 64, device=DEV))
+    y = torch.empty_like(x)
+    c.silu(x, out=y)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        c.silu(x, out=y)
+    for seed in range(3):
+        x.copy_(torch.randn(4, 256, device=DEV))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, c.silu(x))
+    del graph
+    c.close()
