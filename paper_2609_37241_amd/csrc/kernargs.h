@@ -30,6 +30,10 @@ constexpr int kWideLanes = 1024;
 // MI355X); beyond that many rows each workgroup takes rows b, b + grid, ...
 constexpr int kWideGrid = 256;
 
+// Rows that a workgroup per row holds at once on an MI355X: eight workgroups
+// of 256 on each of its 256 compute units.
+constexpr int64_t kAnyBlockRows = 8 * 256;
+
 // Split norm rows (RN_SPLIT): a row of more than 16 * 256 vectors is held
 // by S = ceil(vectors / kSplitSpan) workgroups of 256 work-items, kSplitVecs
 // vectors per work-item, which exchange their partial sums of squares

@@ -17,6 +17,7 @@ namespace tri {
 namespace dev {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
@@ -150,11 +151,29 @@ __device__ inline float wave_sum(float v) {
   return (r0 + r1) + (r2 + r3);
 }
 
-// float64 butterfly over the 64 lanes (long-row and scalar norm paths).
+// The same in float64 (long rows and rows of any alignment): a double moves
+// between lanes as its two halves.
+template <int CTRL>
+__device__ inline double dpp_mov(double v) {
+  const u32x2 b = __builtin_bit_cast(u32x2, v);
+  u32x2 r;
+  r[0] = __builtin_amdgcn_update_dpp(0, b[0], CTRL, 0xF, 0xF, false);
+  r[1] = __builtin_amdgcn_update_dpp(0, b[1], CTRL, 0xF, 0xF, false);
+  return __builtin_bit_cast(double, r);
+}
+__device__ inline double read_lane(double v, int lane) {
+  const u32x2 b = __builtin_bit_cast(u32x2, v);
+  u32x2 r;
+  r[0] = __builtin_amdgcn_readlane(b[0], lane);
+  r[1] = __builtin_amdgcn_readlane(b[1], lane);
+  return __builtin_bit_cast(double, r);
+}
 __device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  v += dpp_mov<0xB1>(v);
+  v += dpp_mov<0x4E>(v);
+  v += dpp_mov<0x141>(v);
+  v += dpp_mov<0x140>(v);
+  return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
 }
 
 // Sum over aligned groups of n consecutive lanes (n a power of two, at most
@@ -447,7 +466,7 @@ template <int DT, bool RES, bool ANY = false>
 __device__ __forceinline__ void rn_loop_row(const RnArgs &a, int64_t row, double *red) {
   using E = Elt<DT>;
   constexpr int V = E::V;
-  constexpr int B = kRnBatch;
+  constexpr int B = ANY ? kRnBatch / 2 : kRnBatch;
   using vec = typename Select<ANY, typename AnyVec<DT>::type, u32x4>::type;
   const int nvec = a.H / V;
   const int te = nvec * V + int(threadIdx.x);   // ANY: this work-item's tail element
@@ -547,20 +566,26 @@ __device__ __forceinline__ void rn_loop_row(const RnArgs &a, int64_t row, double
   }
 }
 
-// A row of any length that starts at any element, held by one workgroup of
-// 256: work-item t owns vectors t, t + 256, ... (NV of them) and, past the
-// last whole vector, element nvec * V + t. The row is read once; the sum is
-// float64, as in the two-pass form. Up to four vectors per work-item the
-// weights are requested with the row (one memory round trip), beyond that
-// after the reduction (fewer registers).
-template <int DT, int NV, bool RES>
+// A row of any length that starts at any element, held by one workgroup
+// (LANES = 256) or one wavefront (LANES = 64, no barrier): lane t owns vectors
+// t, t + LANES, ... (NV of them) and, past the last whole vector, element
+// nvec * V + t. The row is read once; the sum is
+// float64, as in the two-pass form. Up to two vectors per work-item the
+// weights are requested with the row (one memory round trip). Beyond that
+// the residual and, after the reduction, the weights are taken two or four
+// vectors at a time: the lane then stays within 64 registers, so that eight
+// workgroups fit on a compute unit and their rows' loads, reductions and
+// stores overlap.
+template <int DT, int NV, bool RES, int LANES>
 __device__ __forceinline__ void rn_any_regs(const RnArgs &a, int64_t row, double *red) {
   using E = Elt<DT>;
   using vec = typename AnyVec<DT>::type;
   constexpr int V = E::V;
-  constexpr bool W0 = NV <= 4;
+  constexpr bool W0 = NV <= 2;
+  constexpr int B = NV < 4 ? NV : (NV == 8 ? 2 : 4);   // residual vectors at a time
+  constexpr int C = NV < 4 ? NV : 4;                    // weight vectors at a time
   const int nvec = a.H / V;
-  const int tid = int(threadIdx.x);
+  const int tid = int(threadIdx.x) & (LANES - 1);
   const int te = nvec * V + tid;
   const bool tail = te < a.H;
   const vec *xr = reinterpret_cast<const vec *>(static_cast<const char *>(a.x) +
@@ -569,49 +594,56 @@ __device__ __forceinline__ void rn_any_regs(const RnArgs &a, int64_t row, double
   u32x4 xv[NV];
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
-    const int vi = tid + kThreads * k;
+    const int vi = tid + LANES * k;
     xv[k] = vi < nvec ? u32x4(xr[vi]) : u32x4{0, 0, 0, 0};
   }
   float xt = tail ? E::ld(xr, te) : 0.0f;
-  u32x4 rv[RES ? NV : 1];
-  float rt = 0.0f;
+  u32x4 wv[W0 ? NV : 1];
   if constexpr (RES) {
     const vec *rr = reinterpret_cast<const vec *>(static_cast<const char *>(a.res) +
                                                   row * a.res_rs * E::ES);
-#pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      const int vi = tid + kThreads * k;
-      rv[k] = vi < nvec ? u32x4(rr[vi]) : u32x4{0, 0, 0, 0};
-    }
-    if (tail) rt = E::ld(rr, te);
-  }
-  u32x4 wv[W0 ? NV : 1];
-  if constexpr (W0) {
-#pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      const int vi = tid + kThreads * k;
-      wv[k] = vi < nvec ? u32x4(wr[vi]) : u32x4{0, 0, 0, 0};
-    }
-  }
-  const float wt = tail ? E::ld(a.w, te) : 0.0f;
-  if constexpr (RES) {
     vec *orow = reinterpret_cast<vec *>(static_cast<char *>(a.res_out) + row * a.ro_rs * E::ES);
+    const float rt = tail ? E::ld(rr, te) : 0.0f;
 #pragma unroll
-    for (int k = 0; k < NV; ++k) {
-      float f[V], g[V];
-      E::unpack(xv[k], f);
-      E::unpack(rv[k], g);
+    for (int k0 = 0; k0 < NV; k0 += B) {
+      u32x4 rv[B];
 #pragma unroll
-      for (int e = 0; e < V; ++e) f[e] += g[e];
-      xv[k] = E::pack(f);
-      const int vi = tid + kThreads * k;
-      if (vi < nvec) orow[vi] = xv[k];
+      for (int k = 0; k < B; ++k) {
+        const int vi = tid + LANES * (k0 + k);
+        rv[k] = vi < nvec ? u32x4(rr[vi]) : u32x4{0, 0, 0, 0};
+      }
+      if constexpr (W0) {
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+          const int vi = tid + LANES * k;
+          wv[k] = vi < nvec ? u32x4(wr[vi]) : u32x4{0, 0, 0, 0};
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < B; ++k) {
+        float f[V], g[V];
+        E::unpack(xv[k0 + k], f);
+        E::unpack(rv[k], g);
+#pragma unroll
+        for (int e = 0; e < V; ++e) f[e] += g[e];
+        xv[k0 + k] = E::pack(f);
+        const int vi = tid + LANES * (k0 + k);
+        if (vi < nvec) orow[vi] = xv[k0 + k];
+      }
+      if constexpr (NV > B) asm volatile("" ::: "memory");   // the next ones after these
     }
     if (tail) {
       xt = E::round(xt + rt);
       E::st(orow, te, xt);
     }
+  } else if constexpr (W0) {
+#pragma unroll
+    for (int k = 0; k < NV; ++k) {
+      const int vi = tid + LANES * k;
+      wv[k] = vi < nvec ? u32x4(wr[vi]) : u32x4{0, 0, 0, 0};
+    }
   }
+  const float wt = tail ? E::ld(a.w, te) : 0.0f;
   double ss = double(xt) * double(xt);
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
@@ -619,45 +651,82 @@ __device__ __forceinline__ void rn_any_regs(const RnArgs &a, int64_t row, double
     E::unpack(xv[k], f);
 #pragma unroll
     for (int e = 0; e < V; ++e) ss += double(f[e]) * double(f[e]);
+    // the output pass unpacks again: the floats are not kept
+    if constexpr (!W0) asm volatile("" : "+v"(xv[k]));
   }
-  ss = block_sum(ss, red);
+  if constexpr (LANES == 64)
+    ss = wave_sum(ss);
+  else
+    ss = block_sum(ss, red);
   const float inv = float(1.0 / sqrt(ss / double(a.H) + double(a.eps)));
   vec *yr = reinterpret_cast<vec *>(static_cast<char *>(a.y) + row * a.y_rs * E::ES);
+  if (tail) E::st(yr, te, (xt * inv) * wt);
 #pragma unroll
-  for (int k = 0; k < NV; ++k) {
-    const int vi = tid + kThreads * k;
-    if (vi < nvec) {
-      float f[V], w[V];
-      E::unpack(xv[k], f);
-      if constexpr (W0)
-        E::unpack(wv[k], w);
-      else
-        E::unpack(u32x4(wr[vi]), w);
+  for (int k0 = 0; k0 < NV; k0 += C) {
+    if constexpr (!W0) {
 #pragma unroll
-      for (int e = 0; e < V; ++e) f[e] = (f[e] * inv) * w[e];
-      yr[vi] = E::pack(f);
+      for (int k = 0; k < C; ++k) {
+        const int vi = tid + LANES * (k0 + k);
+        if (vi < nvec) {
+          float f[V], w[V];
+          E::unpack(xv[k0 + k], f);
+          E::unpack(u32x4(wr[vi]), w);
+#pragma unroll
+          for (int e = 0; e < V; ++e) f[e] = (f[e] * inv) * w[e];
+          yr[vi] = E::pack(f);
+        }
+      }
+      asm volatile("" ::: "memory");
+    } else {
+#pragma unroll
+      for (int k = 0; k < NV; ++k) {
+        const int vi = tid + LANES * k;
+        if (vi < nvec) {
+          float f[V], w[V];
+          E::unpack(xv[k], f);
+          E::unpack(wv[k], w);
+#pragma unroll
+          for (int e = 0; e < V; ++e) f[e] = (f[e] * inv) * w[e];
+          yr[vi] = E::pack(f);
+        }
+      }
     }
   }
-  if (tail) E::st(yr, te, (xt * inv) * wt);
 }
 
-// Rows that are not 16-byte aligned or not whole vectors: in registers up to
-// 2048 vectors (the fewest that hold the row, as registers bound how many
-// workgroups a compute unit runs), two passes beyond. Bound by memory: bf16
-// residual rows of 1536 x 4097 take 10.8 us (4.7 TB/s), against 15.8 us for
-// element-wise accesses in two passes; 512 x 4096 one element off a 16-byte
-// boundary 5.5 against 13.7 us.
+// Rows that are not 16-byte aligned or not whole vectors; the launch has a
+// workgroup per row. In registers up to 2048 vectors (the fewest that hold
+// the row), two passes beyond. Rows of up to 256 vectors take one wavefront
+// each, four to a workgroup, once there are more rows than workgroups fit on
+// the chip (eight per compute unit): all rows then run at once and no lane
+// waits at a barrier; with fewer rows a workgroup per row has them done
+// sooner. (The launch's other workgroups have no row and end.)
+//
+// Bound by memory: bf16 residual rows of 1536 x 4097 take 10.1 us (5.0 TB/s),
+// against 15.7 us for element-wise accesses in two passes (10.7 us where a
+// lane of up to 94 registers left five workgroups to a compute unit);
+// 512 x 4096 one element off a 16-byte boundary 5.4 against 13.7 us; plain
+// rows of 6198 x 1139 8.8 against 15.3 us (9.3 us with a workgroup per row).
 template <int DT, bool RES>
 __device__ __forceinline__ void rn_any_row(const RnArgs &a, int64_t row, double *red) {
   const int nvec = a.H / Elt<DT>::V;
-  if (nvec <= kThreads)
-    rn_any_regs<DT, 1, RES>(a, row, red);
+  if (nvec <= 256 && a.T > kAnyBlockRows) {
+    row = row * 4 + (threadIdx.x >> 6);
+    if (row >= a.T) return;
+    if (nvec <= 64)
+      rn_any_regs<DT, 1, RES, 64>(a, row, red);
+    else if (nvec <= 128)
+      rn_any_regs<DT, 2, RES, 64>(a, row, red);
+    else
+      rn_any_regs<DT, 4, RES, 64>(a, row, red);
+  } else if (nvec <= kThreads)
+    rn_any_regs<DT, 1, RES, kThreads>(a, row, red);
   else if (nvec <= 2 * kThreads)
-    rn_any_regs<DT, 2, RES>(a, row, red);
+    rn_any_regs<DT, 2, RES, kThreads>(a, row, red);
   else if (nvec <= 4 * kThreads)
-    rn_any_regs<DT, 4, RES>(a, row, red);
+    rn_any_regs<DT, 4, RES, kThreads>(a, row, red);
   else if (nvec <= 8 * kThreads)
-    rn_any_regs<DT, 8, RES>(a, row, red);
+    rn_any_regs<DT, 8, RES, kThreads>(a, row, red);
   else
     rn_loop_row<DT, RES, true>(a, row, red);
 }

@@ -197,3 +197,34 @@ def test_rope_heads(cache, dtype, hd, rd, nq, nk, inter, qkn):
         if nk:
             check("k", host(kd), wk, dtype)
             untouched(kd, kbuf)
+
+
+@pytest.mark.parametrize("res", [False, True], ids=["rmsnorm", "residual"])
+@pytest.mark.parametrize("dtype", [nm.F32, nm.BF16])
+@pytest.mark.parametrize("vecs,tail", [(0, 3), (64, 0), (64, 1), (128, 3), (129, 0), (256, 2)])
+def test_many_short_norm_rows(cache, dtype, vecs, tail, res):
+    """More rows than workgroups fit on the chip at once (2049 of them: the
+    last workgroup has one row): a wavefront per row, against the oracle, and
+    against a call of 2048 rows (a workgroup per row)."""
+    H = vecs * (4 if dtype == nm.F32 else 8) + tail
+    r, T = rng(H), 2049
+    x, rr = wl.host_array(r, (T, H), dtype), wl.host_array(r, (T, H), dtype)
+    w = wl.host_weight(r, H, dtype)
+    xd, _ = put(x, dtype, 1, 1)
+    rd, _ = put(rr, dtype, 2, 0)
+    wd = put(w[None], dtype, 3, 0)[0][0]
+    yd, ybuf = put(np.zeros_like(x), dtype, 1, 2)
+    if res:
+        od, obuf = put(np.zeros_like(x), dtype, 0, 1)
+        cache.residual_rmsnorm(xd, rd, wd, 1e-6, out=yd, residual_out=od)
+        wy, wh = O.residual_rmsnorm(x, rr, w, 1e-6, dtype)
+        check("res_out", host(od), wh, dtype, exact=True)
+        untouched(od, obuf)
+        few = cache.residual_rmsnorm(xd[1:], rd[1:], wd, 1e-6)[0]
+    else:
+        cache.rmsnorm(xd, wd, 1e-6, out=yd)
+        wy = O.rmsnorm(x, w, 1e-6, dtype)
+        few = cache.rmsnorm(xd[1:], wd, 1e-6)
+    check("y", host(yd), wy, dtype)
+    check("y of 2048 rows", host(few), wy[1:], dtype)
+    untouched(yd, ybuf)
