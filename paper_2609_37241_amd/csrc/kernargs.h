@@ -18,9 +18,11 @@ constexpr uint32_t kRopeInterleaved = 1, kRopePos64 = 2, kRopeCache = 4;
 constexpr uint32_t kRopeSliceShift = 8, kRopeTokensShift = 16;
 constexpr int kRopeTokensMax = 4;
 
-// A call that moves more bytes than this streams nontemporally (SwiGLU, the
-// fused chain): beyond the 256 MiB last-level cache and what of it survives
-// from call to call.
+// The last-level cache of an MI355X.
+constexpr uint64_t kCacheBytes = uint64_t(256) << 20;
+// A call that moves more bytes than this streams nontemporally (SwiGLU,
+// residual norms, the fused chain): beyond the last-level cache and what of
+// it survives from call to call.
 constexpr uint64_t kStreamBytes = uint64_t(320) << 20;
 
 // Work-items of the wide norm workgroup (RN_WIDE): one row of up to

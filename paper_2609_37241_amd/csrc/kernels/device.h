@@ -1463,12 +1463,23 @@ __device__ __forceinline__ void elt_flat_part(const EltArgs &a, int64_t blk, int
   }
 }
 
+// Element-wise calls that move more than the 256 MiB last-level cache stream
+// nontemporally. add of bf16 8192-wide rows, cached against nontemporal, the
+// same buffers in each call / three sets in turn: 192 MiB 28.5-30.8 /
+// 36.9-32.4 us, 288 MiB 43.8-46.6 / 53.8-48.0 us, 384 MiB 71.6-62.1 /
+// 71.1-63.8 us; add and a silu that reads its sum (288 + 192 MiB, a call's
+// mean): 40.2-40.0 / 45.4-40.6 us.
+template <int DT, int OP>
+__device__ __forceinline__ bool elt_streams(const EltArgs &a) {
+  return (OP == kOpAdd ? 3 : 2) * a.T * a.W * Elt<DT>::ES > int64_t(kCacheBytes);
+}
+
 // Rows with padded strides: aligned and whole vectors long, or of any start
 // and length (ANY). Bound by memory: masked_fill of bf16 8008 x 1001 takes
 // 7.6 us (5.3 TB/s, a contiguous Python call), against 19.7 us element by
 // element with a 64-bit division each.
-template <int DT, int OP, bool ANY>
-__device__ __forceinline__ void elt_rows_part(const EltArgs &a, int64_t blk, int64_t nblk) {
+template <int DT, int OP, bool ANY, bool NT>
+__device__ __forceinline__ void elt_slots(const EltArgs &a, int64_t blk, int64_t nblk) {
   using E = Elt<DT>;
   constexpr int V = E::V;
   constexpr int BS = OP == kOpMaskedFill ? 1 : E::ES;
@@ -1481,8 +1492,8 @@ __device__ __forceinline__ void elt_rows_part(const EltArgs &a, int64_t blk, int
     const char *b = static_cast<const char *>(a.b) + row * a.b_rs * BS;
     char *o = static_cast<char *>(a.out) + row * a.o_rs * E::ES;
     if (!ANY || e0 + V <= sl.W) {
-      const u32x4 xv = ld_slot<DT, ANY, false>(x, e0);
-      st_slot<DT, ANY, false>(o, e0, elt_vector<DT, OP, ANY, false>(xv, b, e0, fill));
+      const u32x4 xv = ld_slot<DT, ANY, NT>(x, e0);
+      st_slot<DT, ANY, NT>(o, e0, elt_vector<DT, OP, ANY, NT>(xv, b, e0, fill));
     } else {
       const int m = int(sl.W - e0);   // 1 .. V - 1
 #pragma unroll
@@ -1490,6 +1501,14 @@ __device__ __forceinline__ void elt_rows_part(const EltArgs &a, int64_t blk, int
         if (e < m) elt_element<DT, OP>(x, b, o, e0 + e, fill);
     }
   }
+}
+
+template <int DT, int OP, bool ANY>
+__device__ __forceinline__ void elt_rows_part(const EltArgs &a, int64_t blk, int64_t nblk) {
+  if (elt_streams<DT, OP>(a))
+    elt_slots<DT, OP, ANY, true>(a, blk, nblk);
+  else
+    elt_slots<DT, OP, ANY, false>(a, blk, nblk);
 }
 
 // Embedding: workgroup b of nblk copies output rows b, b + nblk, ...; the
@@ -1531,9 +1550,20 @@ __device__ __forceinline__ void body_rn_wave(const RnArgs &a) {
   rn_wave_block<DT, NV, RES, false>(a, blockIdx.x);
 }
 
+// Residual rows of calls that move more than kStreamBytes are read and
+// written nontemporally (bf16 8192 x 8192, three buffer sets in turn: 88.0
+// against 91.9 us; 4096 rows, which fit the last-level cache when the same
+// buffers come again: 44.6 against 38.8 us then, so not below). Plain rows
+// gained nothing at any size (256-512 MiB: 46.3-46.0 and 98.5-100.2 us).
 template <int DT, int NB, bool RES>
 __device__ __forceinline__ void body_rn_block(const RnArgs &a) {
   __shared__ float red[4];
+  if constexpr (RES) {
+    if (4 * a.T * a.H * Elt<DT>::ES > int64_t(kStreamBytes)) {
+      rn_row_regs<DT, NB, RES, 256, true>(a, blockIdx.x, threadIdx.x, red);
+      return;
+    }
+  }
   rn_row_regs<DT, NB, RES, 256, false>(a, blockIdx.x, threadIdx.x, red);
 }
 
@@ -1799,10 +1829,13 @@ __device__ __forceinline__ void body_sw_scalar(const SwArgs &a, uint32_t nblk = 
   sw_rows_part<DT, true>(a, blockIdx.x, nblk);
 }
 
-// U vectors per work-item, cached loads and stores.
+// U vectors per work-item, nontemporal when the call streams (elt_streams).
 template <int DT, int OP, int U>
 __device__ __forceinline__ void body_elt_flat(const EltArgs &a, uint32_t nblk = gridDim.x) {
-  elt_flat_part<DT, OP, false, U>(a, blockIdx.x, nblk);
+  if (elt_streams<DT, OP>(a))
+    elt_flat_part<DT, OP, true, U>(a, blockIdx.x, nblk);
+  else
+    elt_flat_part<DT, OP, false, U>(a, blockIdx.x, nblk);
 }
 
 template <int DT, int OP>
@@ -1836,19 +1869,21 @@ __device__ __forceinline__ void body_emb(const EmbArgs &a, uint32_t nblk = gridD
 // for SwiGLU first or with two / four vectors per work-item.
 //
 // In the streaming form (NT: calls that move more than the last-level
-// cache) the RoPE role also streams nontemporally and keeps one head item
+// cache) the norm and RoPE roles also stream nontemporally (the norm's share:
+// 371.3 against 357.6 us at 8192 tokens, hidden 8192, three buffer sets in
+// turn), and the RoPE role keeps one head item
 // per work-item in flight instead of four: its 77 registers per lane
 // (four items) capped the whole fused kernel at 6 wavefronts per SIMD where
 // SwiGLU alone runs 8, and in alternating launches at 8192 tokens the
 // lighter role took the chain from 357 to 346.5 us (the decode form keeps
 // four items in flight, which its latency needs).
-template <int DT, bool WAVE, int N>
+template <int DT, bool WAVE, int N, bool NT>
 __device__ __forceinline__ void chain_norm_role(const ChainArgs &a, uint32_t blk) {
   if constexpr (WAVE) {
-    rn_wave_block<DT, N, true, false>(a.rn, blk);
+    rn_wave_block<DT, N, true, NT>(a.rn, blk);
   } else {
     __shared__ float red[4];
-    rn_row_regs<DT, N, true, 256, false>(a.rn, blk, threadIdx.x, red);
+    rn_row_regs<DT, N, true, 256, NT>(a.rn, blk, threadIdx.x, red);
   }
 }
 
@@ -1862,7 +1897,7 @@ __device__ __forceinline__ void body_chain(const ChainArgs &a, uint32_t nblk) {
   const uint32_t b = blockIdx.x;
   const uint32_t R = a.rn_blocks, P = a.rope_blocks, S = nblk - R - P;
   if (b < R) {
-    chain_norm_role<DT, WAVE, N>(a, b);
+    chain_norm_role<DT, WAVE, N, NT>(a, b);
   } else if (b < R + P) {
     rope_vec_block<DT, NT, NT ? 1 : 4, QKN, INTER>(a.rope, b - R, lds);
   } else {

@@ -228,3 +228,38 @@ def test_many_short_norm_rows(cache, dtype, vecs, tail, res):
     check("y", host(yd), wy, dtype)
     check("y of 2048 rows", host(few), wy[1:], dtype)
     untouched(yd, ybuf)
+
+
+@pytest.mark.parametrize("op,dtype,T,W,pad", [
+    ("add", nm.BF16, 4500, 10007, 0), ("add", nm.F32, 2000, 12000, 0),
+    ("silu", nm.BF16, 8200, 8200, 8), ("masked_fill", nm.BF16, 9000, 8000, 0),
+    ("residual", nm.BF16, 6000, 8192, 0), ("residual", nm.F32, 6000, 4100, 4)])
+def test_streaming_calls_equal_cached_ones(cache, op, dtype, T, W, pad):
+    """Calls beyond the last-level cache (nontemporal accesses), flat and by
+    rows: the bits of the same call made 1000 rows at a time, and the oracle's
+    values on sampled rows."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(W)
+    td = torch.bfloat16 if dtype == nm.BF16 else torch.float32
+
+    def draw():
+        return torch.randn((T, W + pad), generator=g, device=DEV).to(td)[:, :W]
+    a, b = draw(), draw()
+    w = torch.rand(W, generator=g, device=DEV).to(td) + 0.5
+    mask = a > 0.5
+    run = {"add": lambda s: (cache.add(a[s], b[s]),),
+           "silu": lambda s: (cache.silu(a[s]),),
+           "masked_fill": lambda s: (cache.masked_fill(a[s], mask[s], -1e4),),
+           "residual": lambda s: cache.residual_rmsnorm(a[s], b[s], w, 1e-6)}[op]
+    whole = run(slice(0, T))
+    for lo in range(0, T, 1000):
+        part = run(slice(lo, lo + 1000))
+        for x, y in zip(whole, part):
+            assert torch.equal(x[lo:lo + 1000], y), lo
+    rows = torch.tensor([0, 1, T // 2, T - 1], device=DEV)
+    ah, bh = host(a[rows]), host(b[rows])
+    want = {"add": lambda: (O.add(ah, bh, dtype),), "silu": lambda: (O.silu(ah, dtype),),
+            "masked_fill": lambda: (O.masked_fill(ah, host(mask[rows].to(torch.uint8)), -1e4, dtype),),
+            "residual": lambda: O.residual_rmsnorm(ah, bh, host(w), 1e-6, dtype)}[op]()
+    for x, y in zip(whole, want):
+        check("rows", host(x[rows]), y, dtype)
