@@ -271,10 +271,10 @@ def call_bytes(key) -> int:
     return 0
 
 
-def slot_grid(v: int, T: int, W: int) -> int:
-    """Row passes: a row is ceil(W / v) slots of v elements, one slot per
-    work-item, the slots of all rows numbered through."""
-    return min(cdiv(T * cdiv(W, v), BLOCK), GRID_CAP)
+def slot_grid(v: int, T: int, W: int, per_item: int = 1) -> int:
+    """Row passes: a row is ceil(W / v) slots of v elements, per_item slots
+    per work-item, the slots of all rows numbered through."""
+    return min(cdiv(T * cdiv(W, v), per_item * BLOCK), GRID_CAP)
 
 
 def sw_role(dtype: int, I: int, flags: int, stream: bool, T: int) -> Tuple[int, int]:
@@ -303,9 +303,10 @@ def elt_role(dtype: int, W: int, flags: int, b: int, T: int) -> Tuple[int, int]:
 
 
 def emb_role(dtype: int, H: int, flags: int, T: int) -> Tuple[int, int]:
-    """One workgroup per output row; vectors when aligned and H % v == 0."""
+    """Two row slots per work-item: aligned vectors when aligned and
+    H % v == 0, element-aligned ones otherwise."""
     v = 16 // elem_size(dtype)
-    return (EMB_VEC if (flags & ALIGN) and H % v == 0 else EMB_SCALAR), max(1, min(T, GRID_CAP))
+    return (EMB_VEC if (flags & ALIGN) and H % v == 0 else EMB_SCALAR), slot_grid(v, T, H, 2)
 
 
 # ---- calls -------------------------------------------------------------------
@@ -934,7 +935,7 @@ def grid_of(variant: int, dt: int, T: int, width: int, slices: int = 1, tokens: 
     if variant == ELT_FLAT_U2:
         return max(1, min(cdiv((T * width) // v, 2 * BLOCK), GRID_CAP))
     if variant in (EMB_VEC, EMB_SCALAR):
-        return max(1, min(T, GRID_CAP))
+        return slot_grid(v, T, width, 2)
     if variant in (SW_ROWS, ELT_ROWS, SW_SCALAR, ELT_SCALAR):
         return slot_grid(v, T, width)
     raise ValueError(variant)

@@ -25,6 +25,11 @@ constexpr uint64_t kCacheBytes = uint64_t(256) << 20;
 // it survives from call to call.
 constexpr uint64_t kStreamBytes = uint64_t(320) << 20;
 
+// Embedding: slots of a 16-byte vector's elements per work-item, and the
+// output bytes beyond which they are written nontemporally.
+constexpr int kEmbSlots = 2;
+constexpr uint64_t kEmbStreamBytes = uint64_t(32) << 20;
+
 // Work-items of the wide norm workgroup (RN_WIDE): one row of up to
 // 8 * kWideLanes 16-byte vectors per workgroup; every other kernel uses 256.
 constexpr int kWideLanes = 1024;

@@ -165,10 +165,10 @@ uint64_t call_bytes(const Key &k) {
 }
 
 // Row passes (rows with padded strides, and rows of any start and length):
-// one slot of a vector's elements per work-item, the rows' slots numbered
-// through.
-uint32_t slot_grid(uint32_t dtype, int64_t T, int64_t W) {
-  return clamp_grid(cdiv(T * cdiv(W, vec_elems(dtype)), kBlock));
+// `per_item` slots of a vector's elements per work-item, the rows' slots
+// numbered through.
+uint32_t slot_grid(uint32_t dtype, int64_t T, int64_t W, int64_t per_item = 1) {
+  return clamp_grid(cdiv(T * cdiv(W, vec_elems(dtype)), per_item * kBlock));
 }
 
 // Flat SwiGLU, one vector per work-item, standalone and as the fused
@@ -201,12 +201,13 @@ Role elt_role(uint32_t dtype, int64_t W, unsigned flags, uint32_t bucket, int64_
   return {(flags & kAlign) && W % v == 0 ? ELT_ROWS : ELT_SCALAR, slot_grid(dtype, T, W)};
 }
 
-// Embedding: one workgroup per output row (grid-stride beyond the cap);
-// 16-byte vectors when table and output rows are aligned and H is a whole
-// number of vectors, elements otherwise.
+// Embedding: kEmbSlots row slots per work-item; aligned ones when table and
+// output rows are aligned and H is a whole number of vectors, element-aligned
+// ones otherwise.
 Role emb_role(uint32_t dtype, int64_t H, unsigned flags, int64_t T) {
   const int64_t v = vec_elems(dtype);
-  return {(flags & kAlign) && H % v == 0 ? EMB_VEC : EMB_SCALAR, clamp_grid(T)};
+  return {(flags & kAlign) && H % v == 0 ? EMB_VEC : EMB_SCALAR,
+          slot_grid(dtype, T, H, kEmbSlots)};
 }
 
 // Workgroups of a role variant for T tokens (I is the row width: the norm
@@ -227,7 +228,7 @@ uint32_t role_grid(int32_t variant, uint32_t dtype, int64_t T, int64_t I, int32_
     case ELT_FLAT_U2:
       return clamp_grid(cdiv((T * I) / vec_elems(dtype), 2 * int64_t(kBlock)));
     case EMB_VEC: case EMB_SCALAR:
-      return clamp_grid(T);
+      return slot_grid(dtype, T, I, kEmbSlots);
     case SW_ROWS: case ELT_ROWS: case SW_SCALAR: case ELT_SCALAR:
       return slot_grid(dtype, T, I);
     default:

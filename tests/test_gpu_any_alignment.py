@@ -263,3 +263,20 @@ def test_streaming_calls_equal_cached_ones(cache, op, dtype, T, W, pad):
             "residual": lambda: O.residual_rmsnorm(ah, bh, host(w), 1e-6, dtype)}[op]()
     for x, y in zip(whole, want):
         check("rows", host(x[rows]), y, dtype)
+
+
+@pytest.mark.parametrize("dtype,H", [(nm.F32, 1), (nm.F32, 4), (nm.F32, 1023), (nm.F32, 2052),
+                                     (nm.BF16, 7), (nm.BF16, 8), (nm.BF16, 4095), (nm.BF16, 4104)])
+@pytest.mark.parametrize("off,pad", [(0, 0), (1, 0), (1, 5)])
+def test_embedding_rows(cache, dtype, H, off, pad):
+    """Rows of less than a vector, of whole vectors and with a tail, below, at
+    and above the 512 slots of a workgroup, ids on both sides of the range."""
+    r = rng(H + off)
+    for T, n in ((1, 3), (37, 11)):
+        table = wl.host_array(r, (n, H), dtype)
+        ids = r.integers(-1, n + 1, size=T).astype(np.int64)
+        td, _ = put(table, dtype, off, pad)
+        od, obuf = put(np.ones((T, H), table.dtype), dtype, 2 * off, pad)
+        cache.embedding(td, torch.from_numpy(ids).to(DEV), out=od)
+        check("embedding", host(od), O.embedding(table, ids, dtype), dtype, exact=True)
+        untouched(od, obuf)
