@@ -13,17 +13,22 @@ using namespace dev;
 // workgroup per row); SWV: SW_FLAT or SW_FLAT_NT; QKN: QK norm before the
 // rotation; INTER: GPT-J pairs.
 template <int DT, int RNV, int SWV, bool QKN, bool INTER>
-__global__ __launch_bounds__(256) void k_chain(ChainArgs a) {
+__global__ __launch_bounds__(256) void k_chain(ChainArgs) {
   constexpr bool wave = RNV <= RN_WAVE_2;
   constexpr int n = wave ? 1 << (RNV - RN_WAVE_1) : 1 << (RNV - RN_BLOCK_1);
-  body_chain<DT, wave, n, SWV == SW_FLAT_NT, QKN, INTER>(a, gridDim.x);
+  ChainArgs c;
+  uint32_t g;
+  chain_args(c, g);
+  body_chain<DT, wave, n, SWV == SW_FLAT_NT, QKN, INTER>(c, g);
 }
 
 // Resident argument blocks of this dtype's fused chain: one table per GPU,
 // zero at load (every tag unset). In host code the name stands for a
 // host-side shadow, not for device memory: the host writes the table through
-// its device address, never through the name.
-static __device__ __align__(256) ResidentBlock resident_chain_f32[kResidentSlots];
+// its device address, never through the name. Not static: the address of an
+// internal symbol would be loaded from the code object's offset table, a
+// round trip before the block's own.
+__device__ __align__(256) ResidentBlock resident_chain_f32[kResidentSlots];
 
 template <int DT, int RNV, int SWV, bool QKN, bool INTER>
 __global__ __launch_bounds__(256) void k_chain_res() {

@@ -31,9 +31,9 @@ __global__ __launch_bounds__(256) void k_emb(EmbArgs a) {
 // Resident argument blocks of the element-wise and embedding kernels: one
 // table per family and GPU, dtype major, zero at load. In host code the
 // names stand for host-side shadows; the host writes the tables through
-// their device addresses.
-static __device__ __align__(256) ResidentBlock resident_elt[2 * kResidentSlots];
-static __device__ __align__(256) ResidentBlock resident_emb[2 * kResidentSlots];
+// their device addresses. Not static (see the fused chain's table).
+__device__ __align__(256) ResidentBlock resident_elt[2 * kResidentSlots];
+__device__ __align__(256) ResidentBlock resident_emb[2 * kResidentSlots];
 
 template <int DT, int OP, int U>
 __global__ __launch_bounds__(256) void k_elt_flat_res() {

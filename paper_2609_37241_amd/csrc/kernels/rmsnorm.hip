@@ -71,8 +71,9 @@ __global__ __launch_bounds__(256, 8) void k_rn_scalar(RnArgs a) {
 
 // Resident argument blocks of the norm kernels: one table per GPU, dtype
 // major, zero at load. In host code the name stands for a host-side shadow;
-// the host writes the table through its device address.
-static __device__ __align__(256) ResidentBlock resident_norm[2 * kResidentSlots];
+// the host writes the table through its device address. Not static (see the
+// fused chain's table).
+__device__ __align__(256) ResidentBlock resident_norm[2 * kResidentSlots];
 
 template <int DT>
 __device__ __forceinline__ const ResidentBlock *norm_table() {

@@ -22,8 +22,9 @@ __global__ __launch_bounds__(256) void k_rope_scalar(RopeArgs a) {
 
 // Resident argument blocks of the RoPE kernels: one table per GPU, dtype
 // major, zero at load. In host code the name stands for a host-side shadow;
-// the host writes the table through its device address.
-static __device__ __align__(256) ResidentBlock resident_rope[2 * kResidentSlots];
+// the host writes the table through its device address. Not static (see the
+// fused chain's table).
+__device__ __align__(256) ResidentBlock resident_rope[2 * kResidentSlots];
 
 template <int DT, bool QKN, bool INTER>
 __global__ __launch_bounds__(256) void k_rope_vec_res() {

@@ -24,8 +24,9 @@ __global__ __launch_bounds__(256) void k_sw_scalar(SwArgs a) {
 
 // Resident argument blocks of the SwiGLU kernels: one table per GPU, dtype
 // major, zero at load. In host code the name stands for a host-side shadow;
-// the host writes the table through its device address.
-static __device__ __align__(256) ResidentBlock resident_swiglu[2 * kResidentSlots];
+// the host writes the table through its device address. Not static (see the
+// fused chain's table).
+__device__ __align__(256) ResidentBlock resident_swiglu[2 * kResidentSlots];
 
 template <int DT, int U, bool NT>
 __global__ __launch_bounds__(256) void k_sw_flat_res() {
