@@ -1169,12 +1169,8 @@ __device__ __forceinline__ void rope_any_block(const RopeArgs &a, int64_t t, flo
 // than by HBM. Below g = -80, 1 + exp(g) is 1 in float32 and silu(g) is
 // g * exp(g); that form keeps the tail where exp(-g) overflows (from
 // g = -88.7 on) and would flush the product to zero although the value is
-// still a normal float32 down to about g = -91.5. The tail is recomputed
-// only where a lane is in it: a select of both forms costs three more
-// vector instructions per element, which the streaming silu kernel
-// measured as 7 % (it sits close to its vector ALU limit), while the
-// branch is skipped whenever no lane of the wavefront is that negative.
-// At g = -inf the tail gives -inf * 0 = NaN, as -inf / (1 + inf) does.
+// still a normal float32 down to about g = -91.5. At g = -inf the tail gives
+// -inf * 0 = NaN, as -inf / (1 + inf) does.
 //
 // exp(-g) itself is 2^th * 2^tl with th = RN(-g * hi), tl = the rest of
 // -g * log2(e) (an fma recovers the product's rounding error, lo carries
@@ -1182,24 +1178,52 @@ __device__ __forceinline__ void rope_any_block(const RopeArgs &a, int64_t t, flo
 // hardware exp2 (v_exp_f32, 1 ulp) and four more instructions instead of
 // the library expf's range reduction. The relative error of silu stays
 // below 2.4e-7 for |g| <= 80 (checked against the float64 value over
-// 3 million arguments, as expf's form gives 1.9e-7). At one token the
-// SwiGLU role is the chain's critical path and runs its instructions back
-// to back on one wavefront per SIMD: the shorter sequence measured 2.37
-// against 2.56 us of device time for the standalone 1-token SwiGLU
-// (rocprofv3, 3000 launches each). g is capped at 100 for the exponent
-// (exp(-100) is far below float32's resolution next to 1), which keeps
-// th and tl finite at g = +inf, where silu is +inf.
-__device__ __forceinline__ float silu(float g) {
+// 3 million arguments, as expf's form gives 1.9e-7). g is capped at 100 for
+// the exponent (exp(-100) is far below float32's resolution next to 1), which
+// keeps th and tl finite at g = +inf, where silu is +inf; v_med3_f32 caps
+// without the quieting instruction that fminf takes first.
+__device__ __forceinline__ float silu_main(float g) {
   constexpr float kLog2eHi = 1.44269502162933349609375f;   // RN_f32(log2 e)
   constexpr float kLog2eLo = 1.925963e-08f;                // log2 e - kLog2eHi
   constexpr float kLn2 = 0.693147180559945309f;
-  const float ng = -__builtin_fminf(g, 100.0f);
+  const float ng = -__builtin_amdgcn_fmed3f(g, -3.402823466e+38f, 100.0f);
   const float th = ng * kLog2eHi;
   const float tl = __builtin_fmaf(ng, kLog2eHi, -th) + ng * kLog2eLo;
   const float e = __builtin_amdgcn_exp2f(th);
-  float r = g * __builtin_amdgcn_rcpf(1.0f + __builtin_fmaf(e * tl, kLn2, e));
-  if (__builtin_expect(g < -80.0f, 0)) r = g * expf(g);
-  return r;
+  return g * __builtin_amdgcn_rcpf(1.0f + __builtin_fmaf(e * tl, kLn2, e));
+}
+
+// silu of N elements in place. The tail is recomputed only where an element
+// is in it (the sign and magnitude of the most negative one, as the largest
+// unsigned bit pattern: one instruction for two elements), once for all N: a
+// test and branch per element kept the elements' exp2 and rcp from
+// overlapping, which at decode sizes, where SwiGLU's one wavefront per SIMD
+// runs its instructions back to back, is on the chain's critical path (32
+// captured 8-token chains 99.4 -> 96.9 us, 8 one-token chains 19.2 -> 18.9 us;
+// silu of bf16 1024 x 4096 from Python 4.67 -> 4.48 us).
+template <int N>
+__device__ __forceinline__ void silu_all(float *g) {
+  constexpr uint32_t kTail = 0xC2A00000u;   // the bits of -80
+  float r[N];
+  uint32_t low = 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    r[i] = silu_main(g[i]);
+    const uint32_t b = __float_as_uint(g[i]);
+    low = b > low ? b : low;
+  }
+  if (__builtin_expect(low > kTail, 0)) {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+      if (g[i] < -80.0f) r[i] = g[i] * expf(g[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) g[i] = r[i];
+}
+
+__device__ __forceinline__ float silu(float g) {
+  silu_all<1>(&g);
+  return g;
 }
 
 __device__ __forceinline__ float silu_mul(float g, float u) {
@@ -1234,8 +1258,9 @@ __device__ __forceinline__ void sw_flat_part(const SwArgs &a, int64_t blk, int64
         float fg[V], fu[V];
         E::unpack(gv[k], fg);
         E::unpack(uv[k], fu);
+        silu_all<V>(fg);
 #pragma unroll
-        for (int e = 0; e < V; ++e) fg[e] = silu_mul(fg[e], fu[e]);
+        for (int e = 0; e < V; ++e) fg[e] *= fu[e];
         st16<NT>(o + idx, E::pack(fg));
       }
     }
@@ -1319,8 +1344,9 @@ __device__ __forceinline__ void sw_slots(const SwArgs &a, int64_t blk, int64_t n
       const u32x4 gv = ld_slot<DT, ANY, NT>(g, e0), uv = ld_slot<DT, ANY, NT>(u, e0);
       E::unpack(gv, fg);
       E::unpack(uv, fu);
+      silu_all<V>(fg);
 #pragma unroll
-      for (int e = 0; e < V; ++e) fg[e] = silu_mul(fg[e], fu[e]);
+      for (int e = 0; e < V; ++e) fg[e] *= fu[e];
       st_slot<DT, ANY, NT>(o, e0, E::pack(fg));
     } else {
       const int m = int(sl.W - e0);   // 1 .. V - 1
@@ -1413,9 +1439,13 @@ __device__ __forceinline__ u32x4 elt_vector(u32x4 x, const void *b, int64_t e, u
   } else {
     float fa[V], fb[V];
     E::unpack(x, fa);
-    if constexpr (OP == kOpAdd) E::unpack(ld_slot<DT, ANY, NT>(b, e), fb);
+    if constexpr (OP == kOpAdd) {
+      E::unpack(ld_slot<DT, ANY, NT>(b, e), fb);
 #pragma unroll
-    for (int i = 0; i < V; ++i) fa[i] = elt_value<OP>(fa[i], OP == kOpAdd ? fb[i] : 0.0f);
+      for (int i = 0; i < V; ++i) fa[i] += fb[i];
+    } else {
+      silu_all<V>(fa);
+    }
     return E::pack(fa);
   }
 }

@@ -280,3 +280,37 @@ def test_embedding_rows(cache, dtype, H, off, pad):
         cache.embedding(td, torch.from_numpy(ids).to(DEV), out=od)
         check("embedding", host(od), O.embedding(table, ids, dtype), dtype, exact=True)
         untouched(od, obuf)
+
+
+@pytest.mark.parametrize("dtype", [nm.F32, nm.BF16])
+def test_silu_tail_beside_ordinary_elements(cache, dtype):
+    """Vectors of which one element, all or none lie in the negative tail,
+    with infinities, NaN and zeros beside it: the oracle's values, and for the
+    ordinary elements the bits they have in a vector without a tail."""
+    v = 4 if dtype == nm.F32 else 8
+    base = np.linspace(-79.5, 90.0, v, dtype=np.float32)
+    rows = [base]
+    for x in (-80.0, -80.5, -88.0, -91.0, -103.0, -3e38, -np.inf, np.inf, np.nan, 0.0, -0.0, 3e38):
+        for i in range(v):
+            row = base.copy()
+            row[i] = x
+            rows.append(row)
+    rows.append(np.full(v, -85.0, np.float32))
+    a = nm.round_to(np.stack(rows), dtype) if dtype == nm.BF16 else np.stack(rows)
+    x = wl.to_torch(a, dtype, DEV)
+    got = cache.silu(x)
+    want = O.silu(a, dtype)
+    fin = np.isfinite(nm.values(want, dtype))
+    g = nm.values(host(got), dtype)
+    assert (np.isnan(g) == np.isnan(nm.values(want, dtype))).all()
+    assert (np.isinf(g) == np.isinf(nm.values(want, dtype))).all()
+    w = nm.values(want, dtype)
+    rel = 4e-7 if dtype == nm.F32 else 2.0 ** -8      # one rounding (f32: the form's own error)
+    tiny = 2.0 ** -126                                 # results below it may flush
+    assert (np.abs(g - w)[fin] <= rel * np.abs(w)[fin] + tiny).all()
+    first = got[0]
+    for i, row in enumerate(rows):
+        same = torch.from_numpy(row == rows[0]).to(DEV)
+        assert torch.equal(got[i][same], first[same]), i
+    up = torch.ones_like(x)
+    torch.testing.assert_close(cache.swiglu(x, up), got, rtol=0, atol=0, equal_nan=True)
