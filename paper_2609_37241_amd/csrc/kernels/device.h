@@ -772,6 +772,143 @@ __device__ __forceinline__ char *rope_head(const RopeArgs &a, int64_t t, int h, 
                   : static_cast<char *>(a.k) + (t * a.k_ts + int64_t(h - a.nq) * a.hd) * es;
 }
 
+// One token's heads hg, hg + hstep, ... (of all its Q and K heads) by the
+// group of cpb lanes of which this lane is number `chunk` (see
+// rope_vec_block). The token is the same for the whole workgroup, so its row
+// addresses and its position are scalar work and a lane adds one 32-bit
+// offset; PF heads are requested at a time, the first ones before the angle
+// math and the barrier, with the angle operands ahead of them.
+//
+// Bound by latency at decode sizes: with 64-bit addresses per head and four
+// heads requested where a group has one, some 250 instructions preceded the
+// last load. 8 one-token chains 18.9 -> 16.9 us, 32 captured 8-token chains
+// 96.9 -> 93.4 us, the 512-token GQA chain 12.3 -> 11.8 us. Two heads at a time
+// beyond decode sizes: four cost 107 instead of 78 registers a lane.
+template <int DT, bool NT, int PF, bool QKN, bool INTER>
+__device__ __forceinline__ void rope_token(const RopeArgs &a, int64_t t, int chunk, int cpb, int hg,
+                                           int hstep, float *lds) {
+  using E = Elt<DT>;
+  constexpr int V = E::V;
+  const int P2 = a.rd >> 1;
+  const int nh = a.nq + a.nk;
+  const int off2 = P2 * E::ES;
+  const int tid = int(threadIdx.x);
+  float *cs = lds, *sn = lds + kRopeTokensMax * 256;
+
+  const bool ang = tid < P2;
+  float c = 1.0f, s = 0.0f, p = 0.0f;
+  if (ang) {
+    const int64_t pos = rope_pos(a, t);
+    if (a.mode & kRopeCache) {
+      const int64_t r = pos < 0 ? 0 : (pos >= a.cs_len ? a.cs_len - 1 : pos);
+      const float *row = a.cos_sin + r * a.rd;
+      c = row[tid];
+      s = row[P2 + tid];
+    } else {
+      p = (a.mode & kRopePos64) ? float(pos) : float(int32_t(pos));
+      c = a.inv_freq[tid];
+    }
+  }
+
+  // Q heads 0 .. nq - 1, K heads nq .. nh - 1 at one stride from kb
+  char *qb = static_cast<char *>(a.q) + t * a.q_ts * E::ES;
+  char *kb = static_cast<char *>(a.k) + (t * a.k_ts - int64_t(a.nq) * a.hd) * E::ES;
+  const uint32_t hbytes = uint32_t(a.hd * E::ES), cbytes = uint32_t(chunk) * 16u;
+  auto head = [&](int h) { return (h < a.nq ? qb : kb) + (uint32_t(h) * hbytes + cbytes); };
+  u32x4 x1[PF], x2[PF];
+  auto gather = [&](int h0) {
+#pragma unroll
+    for (int j = 0; j < PF; ++j) {
+      const int h = h0 + j * hstep;
+      if (h < nh) {
+        const char *b = head(h);
+        x1[j] = ld16<NT>(reinterpret_cast<const u32x4 *>(b));
+        if constexpr (!INTER) x2[j] = ld16<NT>(reinterpret_cast<const u32x4 *>(b + off2));
+      }
+    }
+  };
+  gather(hg);
+  u32x4 wq1, wq2, wk1, wk2;
+  if constexpr (QKN) {
+    const char *qw = static_cast<const char *>(a.qw);
+    const char *kw = a.kw ? static_cast<const char *>(a.kw) : qw;
+    wq1 = reinterpret_cast<const u32x4 *>(qw)[chunk];
+    wk1 = reinterpret_cast<const u32x4 *>(kw)[chunk];
+    if constexpr (!INTER) {
+      wq2 = reinterpret_cast<const u32x4 *>(qw + off2)[chunk];
+      wk2 = reinterpret_cast<const u32x4 *>(kw + off2)[chunk];
+    }
+  }
+
+  if (ang) {
+    if (!(a.mode & kRopeCache)) {
+      const float inv = c;
+      sincosf(p * inv, &s, &c);
+    }
+    cs[tid] = c;
+    sn[tid] = s;
+  }
+  __syncthreads();
+
+  for (int h0 = hg; h0 < nh;) {
+#pragma unroll
+    for (int j = 0; j < PF; ++j) {
+      const int h = h0 + j * hstep;
+      if (h >= nh) continue;   // uniform over the lanes of a head group
+      float f1[V], f2[V];
+      E::unpack(x1[j], f1);
+      if constexpr (!INTER) E::unpack(x2[j], f2);
+      if constexpr (QKN) {
+        float ss = 0.0f;
+#pragma unroll
+        for (int e = 0; e < V; ++e) ss = __builtin_fmaf(f1[e], f1[e], ss);
+        if constexpr (!INTER) {
+#pragma unroll
+          for (int e = 0; e < V; ++e) ss = __builtin_fmaf(f2[e], f2[e], ss);
+        }
+        ss = group_sum(ss, cpb);
+        const float inv = rsqrtf(ss / float(a.hd) + a.eps);
+        const bool isq = h < a.nq;
+        float w1[V];
+        E::unpack(isq ? wq1 : wk1, w1);
+#pragma unroll
+        for (int e = 0; e < V; ++e) f1[e] = (f1[e] * inv) * w1[e];
+        if constexpr (!INTER) {
+          float w2[V];
+          E::unpack(isq ? wq2 : wk2, w2);
+#pragma unroll
+          for (int e = 0; e < V; ++e) f2[e] = (f2[e] * inv) * w2[e];
+        }
+      }
+      char *b = head(h);
+      if constexpr (INTER) {
+        const int base = (chunk * V) >> 1;
+        float o[V];
+#pragma unroll
+        for (int e = 0; e < V; e += 2) {
+          const float ce = cs[base + (e >> 1)], se = sn[base + (e >> 1)];
+          o[e] = rot_a(f1[e], f1[e + 1], ce, se);
+          o[e + 1] = rot_b(f1[e], f1[e + 1], ce, se);
+        }
+        st16<NT>(reinterpret_cast<u32x4 *>(b), E::pack(o));
+      } else {
+        const int base = chunk * V;
+        float o1[V], o2[V];
+#pragma unroll
+        for (int e = 0; e < V; ++e) {
+          const float ce = cs[base + e], se = sn[base + e];
+          o1[e] = rot_a(f1[e], f2[e], ce, se);
+          o2[e] = rot_b(f1[e], f2[e], ce, se);
+        }
+        st16<NT>(reinterpret_cast<u32x4 *>(b), E::pack(o1));
+        st16<NT>(reinterpret_cast<u32x4 *>(b + off2), E::pack(o2));
+      }
+    }
+    h0 += PF * hstep;
+    if (h0 < nh) gather(h0);
+  }
+}
+
 // tpb tokens per workgroup (mode bits 16..23, at most kRopeTokensMax; `lds`
 // holds 2 * 256 * kRopeTokensMax floats); with one token per workgroup a
 // token's heads may instead be split round-robin over S = slices workgroups
@@ -811,6 +948,14 @@ __device__ __forceinline__ void rope_vec_block(const RopeArgs &a, int64_t blk, f
   const int64_t tok_blk = S > 1 ? blk / S : blk;
   const int hg = int(blk - tok_blk * S) + S * int(threadIdx.x >> shift);   // first head
   const int hstep = S * (kThreads >> shift);
+  if (tpb == 1) {
+    // at decode sizes the slices leave each group one head
+    if (PF > 1 && hstep >= nh)
+      rope_token<DT, NT, 1, QKN, INTER>(a, tok_blk, chunk, cpb, hg, hstep, lds);
+    else
+      rope_token<DT, NT, PF < 2 ? PF : 2, QKN, INTER>(a, tok_blk, chunk, cpb, hg, hstep, lds);
+    return;
+  }
   const int64_t t0 = tok_blk * tpb;
   const int64_t tlast = a.T - 1;
   float *cs = lds;

@@ -314,3 +314,35 @@ def test_silu_tail_beside_ordinary_elements(cache, dtype):
         assert torch.equal(got[i][same], first[same]), i
     up = torch.ones_like(x)
     torch.testing.assert_close(cache.swiglu(x, up), got, rtol=0, atol=0, equal_nan=True)
+
+
+# Aligned heads, one token to a workgroup: one head per lane group (as many
+# groups as heads, and one more head), several (beyond four slices of 256
+# lanes, and beyond decode sizes), Q and K on either side of a group's step.
+@pytest.mark.parametrize("qkn", [False, True], ids=["plain", "qkn"])
+@pytest.mark.parametrize("inter", [False, True], ids=["half", "pairs"])
+@pytest.mark.parametrize("dtype,T,nq,nk,hd,table", [
+    (nm.BF16, 1, 32, 0, 128, False), (nm.BF16, 1, 32, 1, 128, True), (nm.BF16, 2, 100, 28, 128, True),
+    (nm.BF16, 2, 100, 29, 128, False), (nm.F32, 3, 31, 33, 64, True), (nm.F32, 1, 60, 5, 128, False),
+    (nm.BF16, 70, 32, 1, 128, True), (nm.BF16, 66, 65, 64, 128, False), (nm.F32, 65, 17, 16, 128, False)])
+def test_aligned_rope_tokens(cache, dtype, T, nq, nk, hd, table, inter, qkn):
+    import paper_2609_37241_amd as tri
+    r = rng(T + nq * 3 + hd)
+    q, k = wl.host_array(r, (T, nq, hd), dtype), wl.host_array(r, (T, nk, hd), dtype)
+    qw, kw = wl.host_weight(r, hd, dtype), wl.host_weight(r, hd, dtype)
+    tab = wl.cos_sin_table(r, 300, hd) if table else None
+    pos = r.integers(-2, 310, size=T).astype(np.int64 if table else np.int32)
+    ext = tri.rope_ext(interleaved=inter, pos_int64=table,
+                       cos_sin=torch.from_numpy(tab).to(DEV) if table else None)
+    qd, qbuf = put(q, dtype, 0, 64)
+    kd, kbuf = put(k, dtype, 0, 32) if nk else (None, None)
+    dev = lambda w: wl.to_torch(w, dtype, DEV)
+    cache.rope(qd, kd, torch.from_numpy(pos).to(DEV), 1e4, ext, q_w=dev(qw) if qkn else None,
+               k_w=dev(kw) if qkn and nk else None)
+    wq, wk = O.rope_ext(q, k, pos, 1e4, dtype, q_w=qw if qkn else None, k_w=kw if qkn else None,
+                        eps=1e-6, interleaved=inter, cos_sin=tab)
+    check("q", host(qd), wq, dtype)
+    untouched(qd, qbuf)
+    if nk:
+        check("k", host(kd), wk, dtype)
+        untouched(kd, kbuf)
