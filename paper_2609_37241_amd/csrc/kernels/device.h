@@ -211,6 +211,39 @@ __device__ inline T block_sum(T v, T *red) {
   return s;
 }
 
+// The same for the last sum a workgroup makes with `red` (it is not free again
+// afterwards): one barrier.
+template <typename T>
+__device__ inline T block_sum_once(T v, T *red) {
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// acc + the squares of a vector's N floats in float64. The products are exact
+// in float64, so the fused form rounds as a product and a sum do; two chains
+// of them run side by side.
+template <int N>
+__device__ inline void add_squares(double *acc, const float *f) {
+#pragma unroll
+  for (int e = 0; e < N; ++e) acc[e & 1] = __builtin_fma(double(f[e]), double(f[e]), acc[e & 1]);
+}
+
+// RN_f32(1 / sqrt(m)) for m = ss / H + eps, up to the last bit of the double
+// before rounding: the hardware's reciprocal square root and one Newton step
+// (v_rsq_f64 is good to 2^-24, the step squares that) instead of a
+// division, a square root and another division, about 100 dependent float64
+// instructions between a row's sum and its first store. 0 and infinity, where
+// the step has 0 * infinity in it, keep the first value.
+__device__ inline float inv_rms(double ss, double rcp_h, float eps) {
+  const double m = __builtin_fma(ss, rcp_h, double(eps));
+  const double y = __builtin_amdgcn_rsq(m);
+  const double e = __builtin_fma(-m * y, y, 1.0);
+  const double r = __builtin_fma(0.5 * y, e, y);
+  return float(__builtin_isfinite(r) ? r : y);
+}
+
 // ---- RMSNorm / residual RMSNorm --------------------------------------------------
 // One row held in registers: lane `lane` of LANES owns vectors lane + LANES*k,
 // k < NV. With RES, h = RN(x + r) is written to res_out and normalised.
@@ -275,6 +308,8 @@ __device__ __forceinline__ void rn_row_regs(const RnArgs &a, int64_t row, int la
   }
   if constexpr (LANES == 64)
     ss = wave_sum(ss);
+  else if constexpr (LANES == kThreads)
+    ss = block_sum_once(ss, red);
   else
     ss = block_sum<LANES / 64>(ss, red);
   const float inv = rsqrtf(ss / float(a.H) + a.eps);
@@ -600,6 +635,8 @@ __device__ __forceinline__ void rn_any_regs(const RnArgs &a, int64_t row, double
     xv[k] = vi < nvec ? u32x4(xr[vi]) : u32x4{0, 0, 0, 0};
   }
   float xt = tail ? E::ld(xr, te) : 0.0f;
+  double rcp_h = 1.0 / double(a.H);   // while the row is under way
+  asm volatile("" : "+v"(rcp_h));
   u32x4 wv[W0 ? NV : 1];
   if constexpr (RES) {
     const vec *rr = reinterpret_cast<const vec *>(static_cast<const char *>(a.res) +
@@ -646,21 +683,21 @@ __device__ __forceinline__ void rn_any_regs(const RnArgs &a, int64_t row, double
     }
   }
   const float wt = tail ? E::ld(a.w, te) : 0.0f;
-  double ss = double(xt) * double(xt);
+  double acc[2] = {double(xt) * double(xt), 0.0};
 #pragma unroll
   for (int k = 0; k < NV; ++k) {
     float f[V];
     E::unpack(xv[k], f);
-#pragma unroll
-    for (int e = 0; e < V; ++e) ss += double(f[e]) * double(f[e]);
+    add_squares<V>(acc, f);
     // the output pass unpacks again: the floats are not kept
     if constexpr (!W0) asm volatile("" : "+v"(xv[k]));
   }
+  double ss = acc[0] + acc[1];
   if constexpr (LANES == 64)
     ss = wave_sum(ss);
   else
-    ss = block_sum(ss, red);
-  const float inv = float(1.0 / sqrt(ss / double(a.H) + double(a.eps)));
+    ss = block_sum_once(ss, red);
+  const float inv = inv_rms(ss, rcp_h, a.eps);
   vec *yr = reinterpret_cast<vec *>(static_cast<char *>(a.y) + row * a.y_rs * E::ES);
   if (tail) E::st(yr, te, (xt * inv) * wt);
 #pragma unroll
@@ -707,8 +744,9 @@ __device__ __forceinline__ void rn_any_regs(const RnArgs &a, int64_t row, double
 // Bound by memory: bf16 residual rows of 1536 x 4097 take 10.1 us (5.0 TB/s),
 // against 15.7 us for element-wise accesses in two passes (10.7 us where a
 // lane of up to 94 registers left five workgroups to a compute unit);
-// 512 x 4096 one element off a 16-byte boundary 5.4 against 13.7 us; plain
-// rows of 6198 x 1139 8.8 against 15.3 us (9.3 us with a workgroup per row).
+// 512 x 4096 one element off a 16-byte boundary 5.4 against 12.4 us; plain
+// rows of 6198 x 1139 8.3 against 15.3 us (9.3 us with a workgroup per row and
+// the library's float64 division and square root).
 template <int DT, bool RES>
 __device__ __forceinline__ void rn_any_row(const RnArgs &a, int64_t row, double *red) {
   const int nvec = a.H / Elt<DT>::V;
