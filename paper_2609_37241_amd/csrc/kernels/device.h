@@ -810,21 +810,25 @@ __device__ __forceinline__ char *rope_head(const RopeArgs &a, int64_t t, int h, 
                   : static_cast<char *>(a.k) + (t * a.k_ts + int64_t(h - a.nq) * a.hd) * es;
 }
 
-// One token's heads hg, hg + hstep, ... (of all its Q and K heads) by the
-// group of cpb lanes of which this lane is number `chunk` (see
-// rope_vec_block). The token is the same for the whole workgroup, so its row
-// addresses and its position are scalar work and a lane adds one 32-bit
-// offset; PF heads are requested at a time, the first ones before the angle
-// math and the barrier, with the angle operands ahead of them.
+// Heads hg, hg + hstep, ... of ntok tokens from t on (all Q and K heads of the
+// first token, then of the second, ...) by the group of cpb lanes of which
+// this lane is number `chunk` (see rope_vec_block). With one token (MULTI
+// false) it is the same for the whole workgroup, so its row addresses and its
+// position are scalar work and a lane adds one 32-bit offset. PF heads are
+// requested at a time, the first ones before the angle math and the barrier,
+// with the angle operands ahead of them.
 //
 // Bound by latency at decode sizes: with 64-bit addresses per head and four
 // heads requested where a group has one, some 250 instructions preceded the
 // last load. 8 one-token chains 18.9 -> 16.9 us, 32 captured 8-token chains
-// 96.9 -> 93.4 us, the 512-token GQA chain 12.3 -> 11.8 us. Two heads at a time
-// beyond decode sizes: four cost 107 instead of 78 registers a lane.
-template <int DT, bool NT, int PF, bool QKN, bool INTER>
-__device__ __forceinline__ void rope_token(const RopeArgs &a, int64_t t, int chunk, int cpb, int hg,
-                                           int hstep, float *lds) {
+// 96.9 -> 90.0 us, the 512-token GQA chain 12.3 -> 11.8 us. Two heads at a time
+// beyond decode sizes: four cost 107 instead of 69 registers a lane. Several
+// tokens are spread over all groups: with the second token's heads left to
+// the first one's groups, four 308-token chains of 16 heads took 24.6 us, now
+// 23.5, and 8192 tokens of 9 heads with their norm and SwiGLU 130.4, now 122.7.
+template <int DT, bool NT, int PF, bool QKN, bool INTER, bool MULTI>
+__device__ __forceinline__ void rope_tokens_block(const RopeArgs &a, int64_t t, int ntok, int chunk,
+                                                  int cpb, int hg, int hstep, float *lds) {
   using E = Elt<DT>;
   constexpr int V = E::V;
   const int P2 = a.rd >> 1;
@@ -833,18 +837,21 @@ __device__ __forceinline__ void rope_token(const RopeArgs &a, int64_t t, int chu
   const int tid = int(threadIdx.x);
   float *cs = lds, *sn = lds + kRopeTokensMax * 256;
 
-  const bool ang = tid < P2;
+  const int n = MULTI ? ntok * nh : nh;         // heads of the workgroup
+  const int na = MULTI ? ntok * P2 : P2;        // angles
+  const int ia = MULTI ? tid & (P2 - 1) : tid;  // P2 is a power of two
+  const bool ang = tid < na;
   float c = 1.0f, s = 0.0f, p = 0.0f;
   if (ang) {
-    const int64_t pos = rope_pos(a, t);
+    const int64_t pos = rope_pos(a, MULTI ? t + (tid >> __builtin_ctz(unsigned(P2))) : t);
     if (a.mode & kRopeCache) {
       const int64_t r = pos < 0 ? 0 : (pos >= a.cs_len ? a.cs_len - 1 : pos);
       const float *row = a.cos_sin + r * a.rd;
-      c = row[tid];
-      s = row[P2 + tid];
+      c = row[ia];
+      s = row[P2 + ia];
     } else {
       p = (a.mode & kRopePos64) ? float(pos) : float(int32_t(pos));
-      c = a.inv_freq[tid];
+      c = a.inv_freq[ia];
     }
   }
 
@@ -852,31 +859,32 @@ __device__ __forceinline__ void rope_token(const RopeArgs &a, int64_t t, int chu
   char *qb = static_cast<char *>(a.q) + t * a.q_ts * E::ES;
   char *kb = static_cast<char *>(a.k) + (t * a.k_ts - int64_t(a.nq) * a.hd) * E::ES;
   const uint32_t hbytes = uint32_t(a.hd * E::ES), cbytes = uint32_t(chunk) * 16u;
-  auto head = [&](int h) { return (h < a.nq ? qb : kb) + (uint32_t(h) * hbytes + cbytes); };
-  u32x4 x1[PF], x2[PF];
+  // the i-th head of the workgroup: its token and number
+  auto token_of = [&](int i) { return MULTI ? int(uint32_t(i) / uint32_t(nh)) : 0; };
+  auto head = [&](int tt, int h) {
+    char *b = (h < a.nq ? qb : kb) + (uint32_t(h) * hbytes + cbytes);
+    if constexpr (MULTI) b += int64_t(tt) * (h < a.nq ? a.q_ts : a.k_ts) * E::ES;
+    return b;
+  };
+  u32x4 x1[PF], x2[PF], w1[QKN ? PF : 1], w2[QKN ? PF : 1];
   auto gather = [&](int h0) {
 #pragma unroll
     for (int j = 0; j < PF; ++j) {
-      const int h = h0 + j * hstep;
-      if (h < nh) {
-        const char *b = head(h);
+      const int i = h0 + j * hstep;
+      if (i < n) {
+        const int tt = token_of(i);
+        const char *b = head(tt, i - tt * nh);
         x1[j] = ld16<NT>(reinterpret_cast<const u32x4 *>(b));
         if constexpr (!INTER) x2[j] = ld16<NT>(reinterpret_cast<const u32x4 *>(b + off2));
+        if constexpr (QKN) {   // the head's chunk of the Q or K weights
+          const char *w = static_cast<const char *>(i - tt * nh < a.nq ? a.qw : a.kw) + cbytes;
+          w1[j] = *reinterpret_cast<const u32x4 *>(w);
+          if constexpr (!INTER) w2[j] = *reinterpret_cast<const u32x4 *>(w + off2);
+        }
       }
     }
   };
   gather(hg);
-  u32x4 wq1, wq2, wk1, wk2;
-  if constexpr (QKN) {
-    const char *qw = static_cast<const char *>(a.qw);
-    const char *kw = a.kw ? static_cast<const char *>(a.kw) : qw;
-    wq1 = reinterpret_cast<const u32x4 *>(qw)[chunk];
-    wk1 = reinterpret_cast<const u32x4 *>(kw)[chunk];
-    if constexpr (!INTER) {
-      wq2 = reinterpret_cast<const u32x4 *>(qw + off2)[chunk];
-      wk2 = reinterpret_cast<const u32x4 *>(kw + off2)[chunk];
-    }
-  }
 
   if (ang) {
     if (!(a.mode & kRopeCache)) {
@@ -886,13 +894,21 @@ __device__ __forceinline__ void rope_token(const RopeArgs &a, int64_t t, int chu
     cs[tid] = c;
     sn[tid] = s;
   }
+  if constexpr (MULTI) {
+    for (int e = tid + kThreads; e < na; e += kThreads) {
+      rope_cos_sin(a, t + (e >> __builtin_ctz(unsigned(P2))), e & (P2 - 1), c, s);
+      cs[e] = c;
+      sn[e] = s;
+    }
+  }
   __syncthreads();
 
-  for (int h0 = hg; h0 < nh;) {
+  for (int h0 = hg; h0 < n;) {
 #pragma unroll
     for (int j = 0; j < PF; ++j) {
-      const int h = h0 + j * hstep;
-      if (h >= nh) continue;   // uniform over the lanes of a head group
+      const int i = h0 + j * hstep;
+      if (i >= n) continue;   // uniform over the lanes of a head group
+      const int tt = token_of(i), h = i - tt * nh;
       float f1[V], f2[V];
       E::unpack(x1[j], f1);
       if constexpr (!INTER) E::unpack(x2[j], f2);
@@ -906,21 +922,19 @@ __device__ __forceinline__ void rope_token(const RopeArgs &a, int64_t t, int chu
         }
         ss = group_sum(ss, cpb);
         const float inv = rsqrtf(ss / float(a.hd) + a.eps);
-        const bool isq = h < a.nq;
-        float w1[V];
-        E::unpack(isq ? wq1 : wk1, w1);
+        float w[V];
+        E::unpack(w1[j], w);
 #pragma unroll
-        for (int e = 0; e < V; ++e) f1[e] = (f1[e] * inv) * w1[e];
+        for (int e = 0; e < V; ++e) f1[e] = (f1[e] * inv) * w[e];
         if constexpr (!INTER) {
-          float w2[V];
-          E::unpack(isq ? wq2 : wk2, w2);
+          E::unpack(w2[j], w);
 #pragma unroll
-          for (int e = 0; e < V; ++e) f2[e] = (f2[e] * inv) * w2[e];
+          for (int e = 0; e < V; ++e) f2[e] = (f2[e] * inv) * w[e];
         }
       }
-      char *b = head(h);
+      char *b = head(tt, h);
       if constexpr (INTER) {
-        const int base = (chunk * V) >> 1;
+        const int base = tt * P2 + ((chunk * V) >> 1);
         float o[V];
 #pragma unroll
         for (int e = 0; e < V; e += 2) {
@@ -930,7 +944,7 @@ __device__ __forceinline__ void rope_token(const RopeArgs &a, int64_t t, int chu
         }
         st16<NT>(reinterpret_cast<u32x4 *>(b), E::pack(o));
       } else {
-        const int base = chunk * V;
+        const int base = tt * P2 + chunk * V;
         float o1[V], o2[V];
 #pragma unroll
         for (int e = 0; e < V; ++e) {
@@ -943,7 +957,7 @@ __device__ __forceinline__ void rope_token(const RopeArgs &a, int64_t t, int chu
       }
     }
     h0 += PF * hstep;
-    if (h0 < nh) gather(h0);
+    if (h0 < n) gather(h0);
   }
 }
 
@@ -956,11 +970,13 @@ __device__ __forceinline__ void rope_token(const RopeArgs &a, int64_t t, int chu
 // cpb = P2/V 16-byte vectors and a work-item holds chunk c of both halves;
 // GPT-J pairs (INTER true): the span is cpb = rd/V vectors of V/2 adjacent
 // pairs each and a work-item holds one. Work-item `tid` owns chunk tid % cpb
-// of heads tid / cpb, tid / cpb + 256 / cpb, ... of every token of the
-// block. Its (token, head) items are processed PF at a time with all loads
-// issued before any use, and the first batch is requested before the angle
-// math and the barrier, so at decode sizes the block costs one memory round
-// trip. Elements past rd are not touched.
+// of heads tid / cpb, tid / cpb + 256 / cpb, ... of the block's tokens,
+// numbered through. A group's heads are processed PF at a time (one where the
+// workgroup has no more heads than groups, as the slices and the tokens of a
+// workgroup are chosen for) with all loads issued before any use, and the
+// first batch is requested before the angle math and the barrier, so at
+// decode sizes the block costs one memory round trip. Elements past rd are
+// not touched.
 //
 // QKN (requires rd == hd): each head is first RMS-normalised over its hd
 // elements with the Q or K head-norm weight. The cpb work-items of a head
@@ -969,170 +985,33 @@ __device__ __forceinline__ void rope_token(const RopeArgs &a, int64_t t, int chu
 // item is valid depends only on the work-item's head group, so the lanes of
 // a group skip or process an item together and every lane a reduction reads
 // from is active. cpb <= 64 (the policy guarantees it).
-template <int DT, bool NT, int PF = 4, bool QKN = false, bool INTER = false>
+template <int DT, bool NT, int PF = 2, bool QKN = false, bool INTER = false>
 __device__ __forceinline__ void rope_vec_block(const RopeArgs &a, int64_t blk, float *lds) {
-  using E = Elt<DT>;
-  constexpr int V = E::V;
-  const int P2 = a.rd >> 1;
-  const int lp = __builtin_ctz(unsigned(P2));
-  const int cpb = (INTER ? a.rd : P2) / V;
+  constexpr int V = Elt<DT>::V;
+  const int cpb = (INTER ? a.rd : a.rd >> 1) / V;
   const int shift = __builtin_ctz(unsigned(cpb));
   const int chunk = threadIdx.x & (cpb - 1);
   const int nh = a.nq + a.nk;
   const int tb = int((a.mode >> kRopeTokensShift) & 0xFFu);
   const int tpb = tb < 1 ? 1 : (tb > kRopeTokensMax ? kRopeTokensMax : tb);
-  const int sb = int((a.mode >> kRopeSliceShift) & 0xFFu);
-  const int S = tpb == 1 && sb > 1 ? sb : 1;
-  const int64_t tok_blk = S > 1 ? blk / S : blk;
-  const int hg = int(blk - tok_blk * S) + S * int(threadIdx.x >> shift);   // first head
-  const int hstep = S * (kThreads >> shift);
+  const int g = int(threadIdx.x >> shift), ng = kThreads >> shift;
   if (tpb == 1) {
-    // at decode sizes the slices leave each group one head
+    const int sb = int((a.mode >> kRopeSliceShift) & 0xFFu);
+    const int S = sb > 1 ? sb : 1;
+    const int64_t t = S > 1 ? blk / S : blk;
+    const int hg = int(blk - t * S) + S * g, hstep = S * ng;
     if (PF > 1 && hstep >= nh)
-      rope_token<DT, NT, 1, QKN, INTER>(a, tok_blk, chunk, cpb, hg, hstep, lds);
+      rope_tokens_block<DT, NT, 1, QKN, INTER, false>(a, t, 1, chunk, cpb, hg, hstep, lds);
     else
-      rope_token<DT, NT, PF < 2 ? PF : 2, QKN, INTER>(a, tok_blk, chunk, cpb, hg, hstep, lds);
-    return;
-  }
-  const int64_t t0 = tok_blk * tpb;
-  const int64_t tlast = a.T - 1;
-  float *cs = lds;
-  float *sn = lds + kRopeTokensMax * 256;
-  const int na = tpb * P2;
-  // byte offset of the second vector of an item (rotate-half: the other half)
-  const int off2 = P2 * E::ES;
-
-  // Head-norm weight chunks of this work-item (Q and K; both halves).
-  u32x4 wq1, wq2, wk1, wk2;
-  if constexpr (QKN) {
-    const char *qw = static_cast<const char *>(a.qw);
-    const char *kw = a.kw ? static_cast<const char *>(a.kw) : qw;
-    wq1 = reinterpret_cast<const u32x4 *>(qw)[chunk];
-    wk1 = reinterpret_cast<const u32x4 *>(kw)[chunk];
-    if constexpr (!INTER) {
-      wq2 = reinterpret_cast<const u32x4 *>(qw + off2)[chunk];
-      wk2 = reinterpret_cast<const u32x4 *>(kw + off2)[chunk];
-    }
-  }
-
-  // Operands of this work-item's angle slot (token t0 + tid / P2, pair
-  // tid % P2); indices are clamped so the loads are always in bounds. The
-  // plain mode (int32 positions, computed angles) requests them before the
-  // gather.
-  const int ia = threadIdx.x & (P2 - 1);
-  const int64_t ta = t0 + (threadIdx.x >> lp);
-  const uint32_t vbits = a.mode & 0xFFu;
-  const bool plain = vbits == 0 || vbits == kRopeInterleaved;
-  int32_t pa = 0;
-  float ina = 0.0f;
-  if (plain) {
-    pa = static_cast<const int32_t *>(a.pos)[ta <= tlast ? ta : tlast];
-    ina = a.inv_freq[ia];
-  }
-
-  int tt = 0, h = hg;
-  const int hfirst = hg < nh ? hg : nh - 1;
-  u32x4 x1[PF], x2[PF];
-  int it[PF], ih[PF];
-  bool ok[PF];
-  auto gather = [&]() {
-#pragma unroll
-    for (int j = 0; j < PF; ++j) {
-      ok[j] = tt < tpb && t0 + tt <= tlast && h < nh;
-      it[j] = ok[j] ? tt : 0;
-      ih[j] = ok[j] ? h : hfirst;
-      const char *b = rope_head(a, t0 + it[j], ih[j], E::ES);
-      x1[j] = ld16<NT>(reinterpret_cast<const u32x4 *>(b) + chunk);
-      if constexpr (!INTER) x2[j] = ld16<NT>(reinterpret_cast<const u32x4 *>(b + off2) + chunk);
-      if (ok[j]) {
-        h += hstep;
-        if (h >= nh) {
-          h = hg;
-          ++tt;
-        }
-      }
-    }
-  };
-  gather();
-
-  if (na <= kThreads) {
-    if (threadIdx.x < na) {
-      float c = 1.0f, s = 0.0f;
-      if (ta <= tlast) {
-        if (plain)
-          sincosf(float(pa) * ina, &s, &c);
-        else
-          rope_cos_sin(a, ta, ia, c, s);
-      }
-      cs[threadIdx.x] = c;
-      sn[threadIdx.x] = s;
-    }
+      rope_tokens_block<DT, NT, PF, QKN, INTER, false>(a, t, 1, chunk, cpb, hg, hstep, lds);
   } else {
-    for (int e = threadIdx.x; e < na; e += kThreads) {
-      const int64_t t = t0 + (e >> lp);
-      float c = 1.0f, s = 0.0f;
-      if (t <= tlast) rope_cos_sin(a, t, e & (P2 - 1), c, s);
-      cs[e] = c;
-      sn[e] = s;
-    }
-  }
-  __syncthreads();
-
-  for (;;) {
-#pragma unroll
-    for (int j = 0; j < PF; ++j) {
-      if (!ok[j]) continue;   // uniform over the lanes of a head group
-      float f1[V], f2[V];
-      E::unpack(x1[j], f1);
-      if constexpr (!INTER) E::unpack(x2[j], f2);
-      if constexpr (QKN) {
-        float ss = 0.0f;
-#pragma unroll
-        for (int e = 0; e < V; ++e) ss = __builtin_fmaf(f1[e], f1[e], ss);
-        if constexpr (!INTER) {
-#pragma unroll
-          for (int e = 0; e < V; ++e) ss = __builtin_fmaf(f2[e], f2[e], ss);
-        }
-        ss = group_sum(ss, cpb);
-        const float inv = rsqrtf(ss / float(a.hd) + a.eps);
-        const bool isq = ih[j] < a.nq;
-        float w1[V];
-        E::unpack(isq ? wq1 : wk1, w1);
-#pragma unroll
-        for (int e = 0; e < V; ++e) f1[e] = (f1[e] * inv) * w1[e];
-        if constexpr (!INTER) {
-          float w2[V];
-          E::unpack(isq ? wq2 : wk2, w2);
-#pragma unroll
-          for (int e = 0; e < V; ++e) f2[e] = (f2[e] * inv) * w2[e];
-        }
-      }
-      char *b = rope_head(a, t0 + it[j], ih[j], E::ES);
-      if constexpr (INTER) {
-        const int base = it[j] * P2 + ((chunk * V) >> 1);
-        float o[V];
-#pragma unroll
-        for (int e = 0; e < V; e += 2) {
-          const float c = cs[base + (e >> 1)], s = sn[base + (e >> 1)];
-          o[e] = rot_a(f1[e], f1[e + 1], c, s);
-          o[e + 1] = rot_b(f1[e], f1[e + 1], c, s);
-        }
-        st16<NT>(reinterpret_cast<u32x4 *>(b) + chunk, E::pack(o));
-      } else {
-        const int base = it[j] * P2 + chunk * V;
-        float o1[V], o2[V];
-#pragma unroll
-        for (int e = 0; e < V; ++e) {
-          const float c = cs[base + e], s = sn[base + e];
-          o1[e] = rot_a(f1[e], f2[e], c, s);
-          o2[e] = rot_b(f1[e], f2[e], c, s);
-        }
-        st16<NT>(reinterpret_cast<u32x4 *>(b) + chunk, E::pack(o1));
-        st16<NT>(reinterpret_cast<u32x4 *>(b + off2) + chunk, E::pack(o2));
-      }
-    }
-    if (!(tt < tpb && t0 + tt <= tlast && hg < nh)) break;
-    gather();
+    const int64_t t = blk * tpb;
+    const int64_t left = a.T - t;
+    const int ntok = left < tpb ? int(left) : tpb;
+    if (PF > 1 && ng >= tpb * nh)
+      rope_tokens_block<DT, NT, 1, QKN, INTER, true>(a, t, ntok, chunk, cpb, g, ng, lds);
+    else
+      rope_tokens_block<DT, NT, PF, QKN, INTER, true>(a, t, ntok, chunk, cpb, g, ng, lds);
   }
 }
 
@@ -2056,7 +1935,7 @@ __device__ __forceinline__ void body_rn_scalar(const RnArgs &a) {
 template <int DT, bool QKN, bool INTER>
 __device__ __forceinline__ void body_rope_vec(const RopeArgs &a) {
   __shared__ float lds[2 * 256 * kRopeTokensMax];
-  rope_vec_block<DT, false, 4, QKN, INTER>(a, blockIdx.x, lds);
+  rope_vec_block<DT, false, 2, QKN, INTER>(a, blockIdx.x, lds);
 }
 
 template <int DT, bool QKN>
@@ -2129,12 +2008,10 @@ __device__ __forceinline__ void body_emb(const EmbArgs &a, uint32_t nblk = gridD
 // In the streaming form (NT: calls that move more than the last-level
 // cache) the norm and RoPE roles also stream nontemporally (the norm's share:
 // 371.3 against 357.6 us at 8192 tokens, hidden 8192, three buffer sets in
-// turn), and the RoPE role keeps one head item
-// per work-item in flight instead of four: its 77 registers per lane
-// (four items) capped the whole fused kernel at 6 wavefronts per SIMD where
-// SwiGLU alone runs 8, and in alternating launches at 8192 tokens the
-// lighter role took the chain from 357 to 346.5 us (the decode form keeps
-// four items in flight, which its latency needs).
+// turn), and the RoPE role keeps one head per lane group in flight instead of
+// two: more registers per lane cap the whole fused kernel below the 8
+// wavefronts per SIMD that SwiGLU alone runs (with four heads and 77
+// registers, 357 against 346.5 us at 8192 tokens).
 template <int DT, bool WAVE, int N, bool NT>
 __device__ __forceinline__ void chain_norm_role(const ChainArgs &a, uint32_t blk) {
   if constexpr (WAVE) {
@@ -2157,7 +2034,7 @@ __device__ __forceinline__ void body_chain(const ChainArgs &a, uint32_t nblk) {
   if (b < R) {
     chain_norm_role<DT, WAVE, N, NT>(a, b);
   } else if (b < R + P) {
-    rope_vec_block<DT, NT, NT ? 1 : 4, QKN, INTER>(a.rope, b - R, lds);
+    rope_vec_block<DT, NT, NT ? 1 : 2, QKN, INTER>(a.rope, b - R, lds);
   } else {
     sw_flat_part<DT, 1, NT>(a.sw, b - R - P, S);
   }

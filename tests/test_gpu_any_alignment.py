@@ -324,7 +324,9 @@ def test_silu_tail_beside_ordinary_elements(cache, dtype):
 @pytest.mark.parametrize("dtype,T,nq,nk,hd,table", [
     (nm.BF16, 1, 32, 0, 128, False), (nm.BF16, 1, 32, 1, 128, True), (nm.BF16, 2, 100, 28, 128, True),
     (nm.BF16, 2, 100, 29, 128, False), (nm.F32, 3, 31, 33, 64, True), (nm.F32, 1, 60, 5, 128, False),
-    (nm.BF16, 70, 32, 1, 128, True), (nm.BF16, 66, 65, 64, 128, False), (nm.F32, 65, 17, 16, 128, False)])
+    (nm.BF16, 70, 32, 1, 128, True), (nm.BF16, 66, 65, 64, 128, False), (nm.F32, 65, 17, 16, 128, False),
+    (nm.BF16, 67, 8, 1, 128, True), (nm.BF16, 131, 16, 0, 128, False), (nm.F32, 65, 2, 1, 512, False),
+    (nm.BF16, 67, 1, 0, 512, True), (nm.BF16, 70, 1, 1, 512, False)])
 def test_aligned_rope_tokens(cache, dtype, T, nq, nk, hd, table, inter, qkn):
     import paper_2609_37241_amd as tri
     r = rng(T + nq * 3 + hd)
