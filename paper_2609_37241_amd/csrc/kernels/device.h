@@ -805,11 +805,6 @@ __device__ __forceinline__ float rot_b(float x, float y, float c, float s) {
   return __builtin_fmaf(y, c, x * s);
 }
 
-__device__ __forceinline__ char *rope_head(const RopeArgs &a, int64_t t, int h, int es) {
-  return h < a.nq ? static_cast<char *>(a.q) + (t * a.q_ts + int64_t(h) * a.hd) * es
-                  : static_cast<char *>(a.k) + (t * a.k_ts + int64_t(h - a.nq) * a.hd) * es;
-}
-
 // Heads hg, hg + hstep, ... of ntok tokens from t on (all Q and K heads of the
 // first token, then of the second, ...) by the group of cpb lanes of which
 // this lane is number `chunk` (see rope_vec_block). With one token (MULTI
@@ -1054,10 +1049,11 @@ __device__ __forceinline__ void st_part(char *head, int e, int m, const float *f
 // elements past rd, which are normalised only, are read again after the sum.
 //
 // Bound by memory latency and the lanes that a group leaves idle: 2048
-// tokens of 64 heads of 96 (bf16, six of eight lanes) take 10.0 us (5.1 TB/s),
+// tokens of 64 heads of 96 (bf16, six of eight lanes) take 9.7 us (5.3 TB/s),
 // against 14.8 us with one element pair per work-item and a division each;
-// 512 tokens of 64 heads of 128 one element off a 16-byte boundary 5.5 us,
-// against 10.3 us.
+// 512 tokens of 64 heads of 128 one element off a 16-byte boundary 4.8 us,
+// against 7.9 us. Held to 64 registers for eight workgroups per compute unit it
+// spills and takes 15.3 us.
 template <int DT, bool QKN, bool INTER, int PF = 2>
 __device__ __forceinline__ void rope_any_block(const RopeArgs &a, int64_t t, float *lds) {
   using E = Elt<DT>;
@@ -1092,29 +1088,27 @@ __device__ __forceinline__ void rope_any_block(const RopeArgs &a, int64_t t, flo
     }
   }
 
-  u32x4 wq1, wq2, wk1, wk2;
-  if constexpr (QKN) {
-    const char *qw = static_cast<const char *>(a.qw);
-    const char *kw = a.kw ? static_cast<const char *>(a.kw) : qw;
-    if (m > 0) {
-      wq1 = ld_part<DT>(qw, e0, m);
-      wk1 = ld_part<DT>(kw, e0, m);
-      if constexpr (!INTER) {
-        wq2 = ld_part<DT>(qw, P2 + e0, m);
-        wk2 = ld_part<DT>(kw, P2 + e0, m);
-      }
-    }
-  }
+  // one token: scalar row addresses and a 32-bit offset per head
+  char *qb = static_cast<char *>(a.q) + t * a.q_ts * E::ES;
+  char *kb = static_cast<char *>(a.k) + (t * a.k_ts - int64_t(a.nq) * a.hd) * E::ES;
+  const uint32_t hbytes = uint32_t(a.hd * E::ES);
+  auto head = [&](int h) { return (h < a.nq ? qb : kb) + uint32_t(h) * hbytes; };
+  auto weights = [&](int h) { return static_cast<const char *>(h < a.nq ? a.qw : a.kw); };
 
-  u32x4 x1[PF], x2[PF];
+  u32x4 x1[PF], x2[PF], w1[QKN ? PF : 1], w2[QKN ? PF : 1];
   auto gather = [&](int h) {
 #pragma unroll
     for (int j = 0; j < PF; ++j) {
       x1[j] = x2[j] = u32x4{0, 0, 0, 0};
       if (m > 0 && h + j * hstep < nh) {
-        const char *b = rope_head(a, t, h + j * hstep, E::ES);
+        const char *b = head(h + j * hstep);
         x1[j] = ld_part<DT>(b, e0, m);
         if constexpr (!INTER) x2[j] = ld_part<DT>(b, P2 + e0, m);
+        if constexpr (QKN) {
+          const char *w = weights(h + j * hstep);
+          w1[j] = ld_part<DT>(w, e0, m);
+          if constexpr (!INTER) w2[j] = ld_part<DT>(w, P2 + e0, m);
+        }
       }
     }
   };
@@ -1131,15 +1125,15 @@ __device__ __forceinline__ void rope_any_block(const RopeArgs &a, int64_t t, flo
   __syncthreads();
 
   // normalise (QKN) and rotate the chunk at element e of the span
-  auto rotate = [&](char *b, int e, int n, float *f1, float *f2, float inv, const u32x4 &w1,
-                    const u32x4 &w2) {
+  auto rotate = [&](char *b, int e, int n, float *f1, float *f2, float inv, const u32x4 &h1,
+                    const u32x4 &h2) {
     if constexpr (QKN) {
       float w[V];
-      E::unpack(w1, w);
+      E::unpack(h1, w);
 #pragma unroll
       for (int i = 0; i < V; ++i) f1[i] = (f1[i] * inv) * w[i];
       if constexpr (!INTER) {
-        E::unpack(w2, w);
+        E::unpack(h2, w);
 #pragma unroll
         for (int i = 0; i < V; ++i) f2[i] = (f2[i] * inv) * w[i];
       }
@@ -1171,14 +1165,14 @@ __device__ __forceinline__ void rope_any_block(const RopeArgs &a, int64_t t, flo
     for (int j = 0; j < PF; ++j) {
       const int h = h0 + j * hstep;
       if (h >= nh) continue;              // uniform over a group
-      char *b = rope_head(a, t, h, E::ES);
+      char *b = head(h);
       float f1[V], f2[V];
       E::unpack(x1[j], f1);
       E::unpack(x2[j], f2);
       float inv = 1.0f;
       const char *hw = nullptr;
       if constexpr (QKN) {
-        hw = static_cast<const char *>(h < a.nq || !a.kw ? a.qw : a.kw);
+        hw = weights(h);
         float ss = 0.0f;
 #pragma unroll
         for (int i = 0; i < V; ++i) ss = __builtin_fmaf(f1[i], f1[i], ss);
@@ -1199,15 +1193,14 @@ __device__ __forceinline__ void rope_any_block(const RopeArgs &a, int64_t t, flo
         inv = rsqrtf(ss / float(a.hd) + a.eps);
       }
       if (m > 0) {
-        const bool isq = h < a.nq;
-        rotate(b, e0, m, f1, f2, inv, QKN && isq ? wq1 : wk1, QKN && isq ? wq2 : wk2);
+        rotate(b, e0, m, f1, f2, inv, w1[QKN ? j : 0], w2[QKN ? j : 0]);
       }
       if constexpr (QKN) {
         if constexpr (INTER) {
           for (int e = e0 + G * V; e < span; e += G * V) {
-            const u32x4 w1 = ld_part<DT>(hw, e, span - e);
+            const u32x4 w = ld_part<DT>(hw, e, span - e);
             E::unpack(ld_part<DT>(b, e, span - e), f1);
-            rotate(b, e, span - e, f1, f2, inv, w1, w1);
+            rotate(b, e, span - e, f1, f2, inv, w, w);
           }
         }
         for (int e = e0; e < pass; e += G * V) {
