@@ -341,7 +341,7 @@ __device__ __forceinline__ void rn_wave_block(const RnArgs &a, int64_t blk) {
 
 // ---- split rows -------------------------------------------------------------------
 // A row of nvec vectors is split over S = ceil(nvec / kSplitSpan)
-// consecutive workgroups (workgroup b: row b / S, slice b % S of
+// consecutive workgroups (workgroup b: row b / S, slice b % S, up to
 // kSplitVecs vectors per work-item). Each holds its slice in registers,
 // reduces its partial sum of squares, publishes it in the row's slot of the
 // scratch buffer and waits until all S slots of the row are full; every
@@ -369,20 +369,24 @@ __device__ __forceinline__ void rn_wave_block(const RnArgs &a, int64_t blk) {
 constexpr int kSplitSpinMax = 1 << 18;
 constexpr uint64_t kSlotFull = uint64_t(1) << 63;
 
-template <int DT, bool RES>
-__device__ __forceinline__ void rn_split_row(const RnArgs &a, uint64_t *scratch) {
+template <int DT, bool RES, bool NT>
+__device__ __forceinline__ void rn_split_row(const RnArgs &a, uint64_t *scratch, float *red,
+                                             float &total) {
   using E = Elt<DT>;
   constexpr int V = E::V;
   constexpr int NB = kSplitVecs;
-  __shared__ float red[4];
-  __shared__ float total;
   const int nvec = a.H / V;
   const int S = (nvec + kSplitSpan - 1) / kSplitSpan;
   const int64_t row = int64_t(blockIdx.x) / S;
   const int s = int(int64_t(blockIdx.x) - row * S);
   uint64_t *slots = scratch + kSplitHeaderWords + row * S;
   uint64_t *count = scratch + kSplitHeaderWords + a.T * S + row;
-  const int v0 = s * kSplitSpan + int(threadIdx.x);
+  // equal slices (whole wavefronts of vectors), so that no workgroup of the
+  // row only waits for the others (bf16 residual rows of 49,408, whose fourth
+  // slice of 2048 vectors would hold 32: 84.2 against 90.1 us at 1061 rows)
+  const int span = ((nvec + S - 1) / S + 63) & ~63;
+  const int v0 = s * span + int(threadIdx.x);
+  const int vend = (s + 1) * span < nvec ? (s + 1) * span : nvec;
   const u32x4 *xr = reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.x) +
                                                      row * a.x_rs * E::ES);
   const u32x4 *wr = static_cast<const u32x4 *>(a.w);
@@ -390,7 +394,7 @@ __device__ __forceinline__ void rn_split_row(const RnArgs &a, uint64_t *scratch)
 #pragma unroll
   for (int k = 0; k < NB; ++k) {
     const int vi = v0 + 256 * k;
-    xv[k] = vi < nvec ? xr[vi] : u32x4{0, 0, 0, 0};
+    xv[k] = vi < vend ? ld16<NT>(xr + vi) : u32x4{0, 0, 0, 0};
   }
   if constexpr (RES) {
     const u32x4 *rr = reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.res) +
@@ -400,7 +404,7 @@ __device__ __forceinline__ void rn_split_row(const RnArgs &a, uint64_t *scratch)
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
       const int vi = v0 + 256 * k;
-      rv[k] = vi < nvec ? rr[vi] : u32x4{0, 0, 0, 0};
+      rv[k] = vi < vend ? ld16<NT>(rr + vi) : u32x4{0, 0, 0, 0};
     }
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
@@ -411,13 +415,13 @@ __device__ __forceinline__ void rn_split_row(const RnArgs &a, uint64_t *scratch)
       for (int e = 0; e < V; ++e) f[e] += g[e];
       xv[k] = E::pack(f);
       const int vi = v0 + 256 * k;
-      if (vi < nvec) orow[vi] = xv[k];
+      if (vi < vend) st16<NT>(orow + vi, xv[k]);
     }
   }
 #pragma unroll
   for (int k = 0; k < NB; ++k) {
     const int vi = v0 + 256 * k;
-    wv[k] = vi < nvec ? wr[vi] : u32x4{0, 0, 0, 0};
+    wv[k] = vi < vend ? wr[vi] : u32x4{0, 0, 0, 0};
   }
   float ss = 0.0f;
 #pragma unroll
@@ -477,13 +481,13 @@ __device__ __forceinline__ void rn_split_row(const RnArgs &a, uint64_t *scratch)
 #pragma unroll
   for (int k = 0; k < NB; ++k) {
     const int vi = v0 + 256 * k;
-    if (vi < nvec) {
+    if (vi < vend) {
       float f[V], w[V];
       E::unpack(xv[k], f);
       E::unpack(wv[k], w);
 #pragma unroll
       for (int e = 0; e < V; ++e) f[e] = (f[e] * inv) * w[e];
-      yr[vi] = E::pack(f);
+      st16<NT>(yr + vi, E::pack(f));
     }
   }
 }
@@ -1912,10 +1916,17 @@ __device__ __forceinline__ void body_rn_wide(const RnArgs &a, uint32_t nblk = gr
   }
 }
 
-// Rows of more than 4096 vectors over several workgroups (rn_split_row).
+// Rows of more than 4096 vectors over several workgroups (rn_split_row);
+// residual calls that move more than kStreamBytes nontemporally (1061 rows of
+// 49,408 bf16: 78.6 against 84.2 us, 700 of 131,072: 126.0 against 135.2 us).
 template <int DT, bool RES>
 __device__ __forceinline__ void body_rn_split(const RnSplitArgs &a) {
-  rn_split_row<DT, RES>(a.rn, a.scratch);
+  __shared__ float red[4];
+  __shared__ float total;
+  if (RES && 4 * a.rn.T * a.rn.H * Elt<DT>::ES > int64_t(kStreamBytes))
+    rn_split_row<DT, RES, RES>(a.rn, a.scratch, red, total);
+  else
+    rn_split_row<DT, RES, false>(a.rn, a.scratch, red, total);
 }
 
 template <int DT, bool RES>

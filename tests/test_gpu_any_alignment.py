@@ -233,11 +233,13 @@ def test_many_short_norm_rows(cache, dtype, vecs, tail, res):
 @pytest.mark.parametrize("op,dtype,T,W,pad", [
     ("add", nm.BF16, 4500, 10007, 0), ("add", nm.F32, 2000, 12000, 0),
     ("silu", nm.BF16, 8200, 8200, 8), ("masked_fill", nm.BF16, 9000, 8000, 0),
-    ("residual", nm.BF16, 6000, 8192, 0), ("residual", nm.F32, 6000, 4100, 4)])
+    ("residual", nm.BF16, 6000, 8192, 0), ("residual", nm.F32, 6000, 4100, 4),
+    # split over 3 and 9 workgroups: slices of 1408 and of 2048 vectors, the last shorter
+    ("residual", nm.BF16, 1500, 32776, 8), ("residual", nm.F32, 400, 65540, 0)])
 def test_streaming_calls_equal_cached_ones(cache, op, dtype, T, W, pad):
     """Calls beyond the last-level cache (nontemporal accesses), flat and by
-    rows: the bits of the same call made 1000 rows at a time, and the oracle's
-    values on sampled rows."""
+    rows: the bits of the same call made 1000 rows (or half the rows) at a time,
+    and the oracle's values on sampled rows."""
     g = torch.Generator(device=DEV)
     g.manual_seed(W)
     td = torch.bfloat16 if dtype == nm.BF16 else torch.float32
@@ -252,10 +254,11 @@ def test_streaming_calls_equal_cached_ones(cache, op, dtype, T, W, pad):
            "masked_fill": lambda s: (cache.masked_fill(a[s], mask[s], -1e4),),
            "residual": lambda s: cache.residual_rmsnorm(a[s], b[s], w, 1e-6)}[op]
     whole = run(slice(0, T))
-    for lo in range(0, T, 1000):
-        part = run(slice(lo, lo + 1000))
+    step = min(1000, T // 2)
+    for lo in range(0, T, step):
+        part = run(slice(lo, lo + step))
         for x, y in zip(whole, part):
-            assert torch.equal(x[lo:lo + 1000], y), lo
+            assert torch.equal(x[lo:lo + step], y), lo
     rows = torch.tensor([0, 1, T // 2, T - 1], device=DEV)
     ah, bh = host(a[rows]), host(b[rows])
     want = {"add": lambda: (O.add(ah, bh, dtype),), "silu": lambda: (O.silu(ah, dtype),),
