@@ -55,6 +55,7 @@ RN_BLOCK = {1: 13, 2: 14, 4: 15, 8: 16, 16: 17}
 RN_LOOP = 18
 RN_WIDE = 19               # 1024-work-item workgroups, a row each, 8 vectors per lane
 WIDE_LANES = 1024
+ANY_BLOCK_VECS = 8 * 256  # longest RN_SCALAR row (vectors) on 256 work-items
 WIDE_ROW_VECS = 8 * WIDE_LANES   # the longest row it holds (16-byte vectors)
 WIDE_PLAIN_VECS = 7 * WIDE_LANES  # plain rows up to here take it by policy
 WIDE_PLAIN_BUCKET = 9             # plain rows up to WIDE_ROW_VECS take it from here
@@ -117,9 +118,14 @@ def cdiv(a: int, b: int) -> int:
     return -(-a // b)
 
 
-def block_of(variant: int) -> int:
-    """Work-items per workgroup: 1024 for the wide norm rows, 256 otherwise."""
-    return WIDE_LANES if variant == RN_WIDE else BLOCK
+def block_of(variant: int, dtype: int = 0, H: int = 0) -> int:
+    """Work-items per workgroup: 1024 for the wide norm rows and for unaligned
+    or ragged rows of more than 2048 vectors, 256 otherwise."""
+    if variant == RN_WIDE:
+        return WIDE_LANES
+    if variant == RN_SCALAR and H // (16 // elem_size(dtype)) > ANY_BLOCK_VECS:
+        return WIDE_LANES
+    return BLOCK
 
 
 def next_pow2(n: int) -> int:
@@ -733,7 +739,7 @@ def plan(key, T: int):
     op, dt, b, fl = f["op"], f["dtype"], f["bucket"], f["flags"]
     if op in (OP_RMSNORM, OP_RES_RMSNORM):
         v, g = rn_role(dt, f["H"], fl, T, b, op == OP_RES_RMSNORM)
-        return v, (0, 0, 0), [(v, g, block_of(v))]
+        return v, (0, 0, 0), [(v, g, block_of(v, dt, f["H"]))]
     inter = bool(f["rope_bits"] & ROPE_INTERLEAVED)
     nh = f["nq"] + f["nk"]
     if op in (OP_ROPE_QK, OP_QK_NORM_ROPE):
@@ -764,8 +770,8 @@ def plan(key, T: int):
              and sw[0] in (SW_FLAT, SW_FLAT_NT))
     if fused:
         return CH_FUSED, roles, [(CH_FUSED, rn[1] + ro[1] + sw[1], BLOCK)]
-    return CH_SEQ, roles, [(rn[0], rn[1], block_of(rn[0])), (ro[0], ro[1], BLOCK),
-                           (sw[0], sw[1], BLOCK)]
+    return CH_SEQ, roles, [(rn[0], rn[1], block_of(rn[0], dt, f["H"])),
+                           (ro[0], ro[1], BLOCK), (sw[0], sw[1], BLOCK)]
 
 
 
@@ -941,10 +947,12 @@ def grid_of(variant: int, dt: int, T: int, width: int, slices: int = 1, tokens: 
     raise ValueError(variant)
 
 
-def cand_plan(key, c: Cand, T: int):
-    """(variant, roles, launches) of candidate c for a call with T tokens, in
-    the form plan() returns."""
+def cand_plan(key, c: Cand, T: int, call_H: Optional[int] = None):
+    """(variant, roles, launches) of candidate c for a call with T tokens (and
+    rows of call_H elements, where a version serves a range), in the form
+    plan() returns."""
     f = unpack_key(key)
+    rn_H = f["H"] if call_H is None else call_H
     dt = f["dtype"]
 
     def width(kv):        # the norm rows' H, a short op's W, else SwiGLU's I
@@ -956,7 +964,8 @@ def cand_plan(key, c: Cand, T: int):
         return CH_FUSED, c.roles, [(CH_FUSED, g, BLOCK)]
     res = f["op"] != OP_RMSNORM           # the chain's norm role is residual
     launches = [(kv, grid_of(kv, dt, T, width(kv), c.slices, c.tokens) if kv in ROPE_VEC_ROLES
-                 else grid_of(kv, dt, T, width(kv), res=res), block_of(kv)) for kv in c.kernels]
+                 else grid_of(kv, dt, T, width(kv), res=res), block_of(kv, dt, rn_H))
+                for kv in c.kernels]
     return c.variant, c.roles, launches
 
 
@@ -1215,7 +1224,7 @@ class SpecCacheModel:
                 return st
             i = self.lookup(key)
             auto = True
-        variant, roles, launches = self.version_plan(i, c.T)
+        variant, roles, launches = self.version_plan(i, c.T, key)
         rec.version, rec.variant, rec.roles = i, variant, roles
         rec.n_launches = len(launches)
         rec.launch = tuple(launches) + ((0, 0, 0),) * (3 - len(launches))
@@ -1284,7 +1293,7 @@ class SpecCacheModel:
         for i, c in enumerate(calls):
             if vis[i] is None:
                 continue
-            variant, roles, launches = self.version_plan(vis[i], c.T)
+            variant, roles, launches = self.version_plan(vis[i], c.T, keys[i])
             st = self._launch(launches)
             total += len(launches)
             if st < 0 or i == last:
@@ -1304,10 +1313,10 @@ class SpecCacheModel:
                     self.version_hits[v] += 1
         return OK
 
-    def version_plan(self, i: int, T: int):
+    def version_plan(self, i: int, T: int, call_key):
         """(variant, roles, launches) of version i for a call with T tokens."""
         key = self.versions[i]
-        return cand_plan(key, candidates(key)[self.choice[i]], T)
+        return cand_plan(key, candidates(key)[self.choice[i]], T, unpack_key(call_key)["H"])
 
     def _install(self, key, candidate: int = -1, generic: bool = False) -> int:
         """Install `key` with candidate plan `candidate` (-1: tuned on a
@@ -1360,7 +1369,7 @@ class SpecCacheModel:
         st = self._install(key, generic=bool(self.flags & FLAG_GENERIC))
         if st < 0:
             return st, None
-        variant, roles, launches = self.version_plan(self.lookup(key), T)
+        variant, roles, launches = self.version_plan(self.lookup(key), T, key)
         rec = Record(op=key[0] & 0xFF, status=OK, version=self.lookup(key),
                      variant=variant, n_launches=len(launches), roles=roles,
                      launch=tuple(launches) + ((0, 0, 0),) * (3 - len(launches)),

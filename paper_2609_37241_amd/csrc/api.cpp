@@ -284,8 +284,6 @@ inline tri_status finish(tri_cache *c, Version &v, bool auto_inst, int rc) {
   return TRI_OK;
 }
 
-inline int64_t vec_elems(uint32_t dtype) { return dtype == TRI_F32 ? 4 : 8; }
-
 // Validation and key of one decode-chain call: kGo with *out set, TRI_OK
 // for T == 0, or an error. Order: common, norm, RoPE, QK norm, SwiGLU.
 int chain_check(const tri_chain_args *p, Key *out) {
@@ -384,7 +382,7 @@ int chain_launch(tri_cache *c, const Version &v, const tri_chain_args &p, void *
   *n = 3;
   int rc = 0;
   for (int i = 0; i < 3; ++i) {
-    l[i] = {v.plan.kvariant[i], grids[i], role_block(v.plan.kvariant[i])};
+    l[i] = {v.plan.kvariant[i], grids[i], role_block(v.plan.kvariant[i], dtype, rn.H)};
     if (rc == 0) rc = launch(c, v, i, dtype, grids[i], l[i].block_x, args[i], sizes[i], stream);
   }
   return rc;
@@ -417,7 +415,7 @@ tri_status single_launch(tri_cache *c, uint32_t op, const Key &k, int64_t T, int
   Version &v = c->versions[vi];
   const tri_launch_rec l{v.plan.kvariant[0],
                          role_grid(v.plan.kvariant[0], key_dtype(k), T, width),
-                         role_block(v.plan.kvariant[0])};
+                         kBlock};
   const int rc = launch(c, v, 0, key_dtype(k), l.grid_x, l.block_x, args, args_size, stream);
   record(c, op, v, vi, k, 1, &l, rc ? TRI_E_LAUNCH : TRI_OK);
   return finish(c, v, auto_inst, rc);
@@ -433,7 +431,7 @@ tri_status norm_launch(tri_cache *c, uint32_t op, const Key &k, const RnArgs &a,
   Version &v = c->versions[vi];
   const int32_t kv = v.plan.kvariant[0];
   const tri_launch_rec l{kv, norm_grid(kv, key_dtype(k), a.T, a.H, op == TRI_OP_RES_RMSNORM),
-                         role_block(kv)};
+                         role_block(kv, key_dtype(k), a.H)};
   int rc;
   if (kv == RN_SPLIT) {
     const RnSplitArgs sa{a, v.d_scratch};
@@ -689,7 +687,8 @@ tri_status tri_residual_rmsnorm_noalloc(tri_cache *c, tri_dtype dtype, const voi
   Version &v = c->versions[vi];
   const int32_t kv = v.plan.kvariant[0];
   const RnArgs a{x, res, w, y, res_out, x_rs, res_rs, y_rs, ro_rs, T, int32_t(H), eps};
-  const tri_launch_rec l{kv, norm_grid(kv, uint32_t(dtype), T, H, true), role_block(kv)};
+  const tri_launch_rec l{kv, norm_grid(kv, uint32_t(dtype), T, H, true),
+                         role_block(kv, uint32_t(dtype), H)};
   // Always with kernel arguments: a resident block's first use copies it
   // to the device, which this entry point does not do.
   int rc;

@@ -310,7 +310,7 @@ void fill_selection(const Version &v, int32_t index, int64_t T, tri_selection *o
                             ? norm_grid(kv, dt, T, launch_width(k, kv), key_op(k) != TRI_OP_RMSNORM)
                             : role_grid(kv, dt, T, launch_width(k, kv), v.plan.rope_slices,
                                         v.plan.rope_tokens),
-                        role_block(kv)};
+                        role_block(kv, dt, key_H(call_key ? *call_key : k))};
     }
   }
   key_words(call_key ? *call_key : k, out->key);

@@ -129,9 +129,14 @@ uint32_t norm_grid(int32_t variant, uint32_t dtype, int64_t T, int64_t H, bool r
 // The row width role_grid takes for launch variant `kv` of a version with key k.
 int64_t launch_width(const Key &k, int32_t kv);
 inline bool is_norm_variant(int32_t v) { return v >= RN_SCALAR && v <= RN_SPLIT; }
-// Work-items per workgroup of a launch of `variant`.
-inline uint32_t role_block(int32_t variant) {
-  return variant == RN_WIDE ? uint32_t(kWideLanes) : kBlock;
+// Elements of a 16-byte vector.
+inline int64_t vec_elems(uint32_t dtype) { return dtype == TRI_F32 ? 4 : 8; }
+// Work-items per workgroup of a launch of `variant` (a norm variant's row
+// width is H).
+inline uint32_t role_block(int32_t variant, uint32_t dtype, int64_t H) {
+  if (variant == RN_WIDE) return uint32_t(kWideLanes);
+  if (variant == RN_SCALAR && H / vec_elems(dtype) > kAnyBlockVecs) return uint32_t(kWideLanes);
+  return kBlock;
 }
 // RoPE vector roles at decode sizes split a token's heads over this many
 // workgroups (1 otherwise).

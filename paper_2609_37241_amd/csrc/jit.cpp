@@ -116,7 +116,7 @@ int kernel_text(const Key &k, const Plan &p, int i, char *o, size_t n) {
   return snprintf(o, n,
                   "\nextern \"C\" __global__ __launch_bounds__(%u) void "
                   "tri_jit_kernel(tri::%s a) {\n%s  tri::dev::%s;\n}\n",
-                  role_block(v), type, shape, body);
+                  role_block(v, dt, key_H(k)), type, shape, body);
 }
 
 }  // namespace

@@ -31,7 +31,8 @@ constexpr int kEmbSlots = 2;
 constexpr uint64_t kEmbStreamBytes = uint64_t(32) << 20;
 
 // Work-items of the wide norm workgroup (RN_WIDE): one row of up to
-// 8 * kWideLanes 16-byte vectors per workgroup; every other kernel uses 256.
+// 8 * kWideLanes 16-byte vectors per workgroup, and of RN_SCALAR's longer
+// rows (kAnyBlockVecs); every other kernel uses 256.
 constexpr int kWideLanes = 1024;
 // Most workgroups of a plain wide-row launch (one per compute unit of an
 // MI355X); beyond that many rows each workgroup takes rows b, b + grid, ...
@@ -40,6 +41,9 @@ constexpr int kWideGrid = 256;
 // Rows that a workgroup per row holds at once on an MI355X: eight workgroups
 // of 256 on each of its 256 compute units.
 constexpr int64_t kAnyBlockRows = 8 * 256;
+// Longest row (16-byte vectors) that RN_SCALAR, the norm of rows of any start
+// and length, holds with a workgroup of 256; longer ones take kWideLanes.
+constexpr int kAnyBlockVecs = 8 * 256;
 
 // Split norm rows (RN_SPLIT): a row of more than 16 * 256 vectors is held
 // by S = ceil(vectors / kSplitSpan) workgroups of 256 work-items, kSplitVecs

@@ -65,7 +65,7 @@ __global__ __launch_bounds__(256) void k_rn_split(RnSplitArgs a) {
 }
 
 template <int DT, bool RES>
-__global__ __launch_bounds__(256, 8) void k_rn_scalar(RnArgs a) {
+__global__ __launch_bounds__(kWideLanes, 8) void k_rn_scalar(RnArgs a) {
   body_rn_scalar<DT, RES>(a);
 }
 
@@ -116,7 +116,7 @@ __global__ __launch_bounds__(256) void k_rn_split_res() {
 }
 
 template <int DT, bool RES>
-__global__ __launch_bounds__(256, 8) void k_rn_scalar_res() {
+__global__ __launch_bounds__(kWideLanes, 8) void k_rn_scalar_res() {
   RnArgs a;
   uint32_t g;
   if (resident_args(norm_table<DT>(), a, g)) body_rn_scalar<DT, RES>(a);

@@ -24,7 +24,6 @@ inline int64_t next_pow2(int64_t n) {
   return p;
 }
 
-inline int64_t vec_elems(uint32_t dtype) { return dtype == TRI_F32 ? 4 : 8; }
 
 inline uint32_t clamp_grid(int64_t g) {
   if (g < 1) return 1;

@@ -58,7 +58,8 @@ def untouched(t, buf):
 # passes beyond.
 def _norm_lengths(v):
     return [v - 1, v, 255 * v + 1, 256 * v, 256 * v + v - 1, 257 * v, 512 * v, 513 * v + 1,
-            1024 * v + 1, 1025 * v, 2048 * v + v - 1, 2049 * v, 4097 * v + 3]
+            1024 * v + 1, 1025 * v, 2048 * v + v - 1, 2049 * v, 4096 * v + 1, 4097 * v + 3,
+            8192 * v + v - 1, 8193 * v, 12289 * v + 1]
 
 
 NORM = [(d, H) for d, v in ((nm.F32, 4), (nm.BF16, 8)) for H in _norm_lengths(v)]
@@ -235,7 +236,10 @@ def test_many_short_norm_rows(cache, dtype, vecs, tail, res):
     ("silu", nm.BF16, 8200, 8200, 8), ("masked_fill", nm.BF16, 9000, 8000, 0),
     ("residual", nm.BF16, 6000, 8192, 0), ("residual", nm.F32, 6000, 4100, 4),
     # split over 3 and 9 workgroups: slices of 1408 and of 2048 vectors, the last shorter
-    ("residual", nm.BF16, 1500, 32776, 8), ("residual", nm.F32, 400, 65540, 0)])
+    ("residual", nm.BF16, 1500, 32776, 8), ("residual", nm.F32, 400, 65540, 0),
+    # ragged: 256 and 1024 work-items a row, and rows held in part
+    ("residual", nm.BF16, 6000, 8195, 0), ("residual", nm.BF16, 1100, 40003, 5),
+    ("residual", nm.F32, 300, 88771, 0)])
 def test_streaming_calls_equal_cached_ones(cache, op, dtype, T, W, pad):
     """Calls beyond the last-level cache (nontemporal accesses), flat and by
     rows: the bits of the same call made 1000 rows (or half the rows) at a time,
