@@ -278,7 +278,7 @@ typedef struct tri_chain_args {
  * list of candidate plans -- index 0 the install policy's plan, then the
  * other kernel variants whose preconditions the key guarantees (another
  * register layout or the two-pass kernel for norm rows, 1 / 2 / 4
- * workgroups per token or the scalar kernel for vector RoPE, the other flat
+ * workgroups per token or the any-alignment kernel for vector RoPE, the other flat
  * form or the row kernel for SwiGLU and the element-wise ops, every
  * combination of those for the fused chain and then its three-launch
  * sequence). Installing a key with more than one candidate makes a tuning
@@ -304,10 +304,10 @@ typedef struct tri_chain_args {
  * creates a generic version: it matches the missed key with any token
  * bucket in the widest run of buckets around the key's over which the
  * install policy picks the same plan, and -- for RMSNorm and residual
- * RMSNorm rows held by one wavefront or one workgroup, or by the scalar
- * kernel -- any hidden size that kernel serves (rows of 1-64, 65-128,
+ * RMSNorm rows held by one wavefront or one workgroup, or unaligned or
+ * ragged -- any hidden size that kernel serves (rows of 1-64, 65-128,
  * 129-256, ..., 2049-4096 16-byte vectors, plain RMSNorm rows also
- * 4097-7168, every length of the scalar kernel's class). A version whose
+ * 4097-7168, every unaligned or every ragged length). A version whose
  * plan (the policy's or a tuned one) splits norm rows over workgroups keeps
  * only the buckets of that run whose split scratch fits (at most 32 MiB,
  * allocated for the top bucket at install), and matches its exact hidden

@@ -20,15 +20,15 @@ constexpr int kRopeTokensMax = 4;
 
 // The last-level cache of an MI355X.
 constexpr uint64_t kCacheBytes = uint64_t(256) << 20;
-// A call that moves more bytes than this streams nontemporally (SwiGLU,
-// residual norms, the fused chain): beyond the last-level cache and what of
+// A call that moves more bytes than this streams nontemporally (SwiGLU, the
+// fused chain; residual norms: their loads): beyond the last-level cache and what of
 // it survives from call to call.
 constexpr uint64_t kStreamBytes = uint64_t(320) << 20;
 
 // Embedding: slots of a 16-byte vector's elements per work-item, and the
 // output bytes beyond which they are written nontemporally.
 constexpr int kEmbSlots = 2;
-constexpr uint64_t kEmbStreamBytes = uint64_t(32) << 20;
+constexpr uint64_t kEmbStreamBytes = kCacheBytes;
 
 // Work-items of the wide norm workgroup (RN_WIDE): one row of up to
 // 8 * kWideLanes 16-byte vectors per workgroup, and of RN_SCALAR's longer

@@ -306,7 +306,7 @@ __device__ __forceinline__ void rn_row_regs(const RnArgs &a, int64_t row, int la
       for (int e = 0; e < V; ++e) f[e] += g[e];
       xv[k] = E::pack(f);
       const int vi = lane + LANES * k;
-      if (vi < nvec) st16<NT>(orow + vi, xv[k]);
+      if (vi < nvec) orow[vi] = xv[k];
     }
   }
   float ss = 0.0f;
@@ -337,7 +337,7 @@ __device__ __forceinline__ void rn_row_regs(const RnArgs &a, int64_t row, int la
         E::unpack(wv[k], w);
 #pragma unroll
       for (int e = 0; e < V; ++e) f[e] = (f[e] * inv) * w[e];
-      st16<NT>(yr + vi, E::pack(f));
+      yr[vi] = E::pack(f);
     }
   }
 }
@@ -426,7 +426,7 @@ __device__ __forceinline__ void rn_split_row(const RnArgs &a, uint64_t *scratch,
       for (int e = 0; e < V; ++e) f[e] += g[e];
       xv[k] = E::pack(f);
       const int vi = v0 + 256 * k;
-      if (vi < vend) st16<NT>(orow + vi, xv[k]);
+      if (vi < vend) orow[vi] = xv[k];
     }
   }
 #pragma unroll
@@ -498,7 +498,7 @@ __device__ __forceinline__ void rn_split_row(const RnArgs &a, uint64_t *scratch,
       E::unpack(wv[k], w);
 #pragma unroll
       for (int e = 0; e < V; ++e) f[e] = (f[e] * inv) * w[e];
-      st16<NT>(yr + vi, E::pack(f));
+      yr[vi] = E::pack(f);
     }
   }
 }
@@ -667,7 +667,7 @@ __device__ __forceinline__ void rn_any_regs(const RnArgs &a, int64_t row, double
         for (int e = 0; e < V; ++e) f[e] += g[e];
         xv[k0 + k] = E::pack(f);
         const int vi = tid + LANES * (k0 + k);
-        if (vi < nvec) st_any<DT, NT>(orow + vi, xv[k0 + k]);
+        if (vi < nvec) orow[vi] = xv[k0 + k];
       }
       if constexpr (NV > B) asm volatile("" ::: "memory");   // the next ones after these
     }
@@ -712,7 +712,7 @@ __device__ __forceinline__ void rn_any_regs(const RnArgs &a, int64_t row, double
           E::unpack(u32x4(wr[vi]), w);
 #pragma unroll
           for (int e = 0; e < V; ++e) f[e] = (f[e] * inv) * w[e];
-          st_any<DT, NT>(yr + vi, E::pack(f));
+          yr[vi] = E::pack(f);
         }
       }
       asm volatile("" ::: "memory");
@@ -726,7 +726,7 @@ __device__ __forceinline__ void rn_any_regs(const RnArgs &a, int64_t row, double
           E::unpack(wv[k], w);
 #pragma unroll
           for (int e = 0; e < V; ++e) f[e] = (f[e] * inv) * w[e];
-          st_any<DT, NT>(yr + vi, E::pack(f));
+          yr[vi] = E::pack(f);
         }
       }
     }
@@ -823,7 +823,7 @@ __device__ __forceinline__ void rn_any_long(const RnArgs &a, int64_t row, double
     E::unpack(wv, w);
 #pragma unroll
     for (int e = 0; e < V; ++e) f[e] = (f[e] * inv) * w[e];
-    st_any<DT, NT>(yr + vi, E::pack(f));
+    yr[vi] = E::pack(f);
   };
   for (int base = NV * LANES + tid; base < nvec; base += LANES * B) {
     u32x4 sv[B], wv[B];
@@ -854,11 +854,11 @@ __device__ __forceinline__ void rn_any_long(const RnArgs &a, int64_t row, double
 
 // Rows that are not 16-byte aligned or not whole vectors; the launch has a
 // workgroup per row. In registers (the fewest that hold the row) up to 2048
-// vectors on 256 work-items and 8192 on 1024, two passes beyond. Rows of up to 256 vectors take one wavefront
-// each, four to a workgroup, once there are more rows than workgroups fit on
-// the chip (eight per compute unit): all rows then run at once and no lane
-// waits at a barrier; with fewer rows a workgroup per row has them done
-// sooner. (The launch's other workgroups have no row and end.)
+// vectors on 256 work-items and 8192 on 1024, two passes beyond. Rows of up to
+// 256 vectors take one wavefront each, four to a workgroup, once there are more
+// rows than workgroups fit on the chip (eight per compute unit): all rows then
+// run at once and no lane waits at a barrier; with fewer rows a workgroup per
+// row has them done sooner. (The launch's other workgroups have no row and end.)
 //
 // Bound by memory: bf16 residual rows of 1536 x 4097 take 10.1 us (5.0 TB/s),
 // against 15.7 us for element-wise accesses in two passes (10.7 us where a
@@ -1668,7 +1668,7 @@ __device__ __forceinline__ void elt_flat_part(const EltArgs &a, int64_t blk, int
 #pragma unroll
     for (int k = 0; k < U; ++k) {
       const int64_t i = base + int64_t(k) * kThreads;
-      if (i < a.nvec) st16<NT>(o + i, elt_vector<DT, OP, false, NT>(xv[k], a.b, i * V, fill));
+      if (i < a.nvec) o[i] = elt_vector<DT, OP, false, NT>(xv[k], a.b, i * V, fill);
     }
   }
   if (blk == 0) {
@@ -1677,12 +1677,12 @@ __device__ __forceinline__ void elt_flat_part(const EltArgs &a, int64_t blk, int
   }
 }
 
-// Element-wise calls that move more than the 256 MiB last-level cache stream
-// nontemporally. add of bf16 8192-wide rows, cached against nontemporal, the
-// same buffers in each call / three sets in turn: 192 MiB 28.5-30.8 /
-// 36.9-32.4 us, 288 MiB 43.8-46.6 / 53.8-48.0 us, 384 MiB 71.6-62.1 /
-// 71.1-63.8 us; add and a silu that reads its sum (288 + 192 MiB, a call's
-// mean): 40.2-40.0 / 45.4-40.6 us.
+// Element-wise calls that move more than the 256 MiB last-level cache read
+// nontemporally and write through it. bf16 add of 4096 x 12288, three buffer
+// sets in turn: 45.3 us, against 53.5 cached and 47.9 nontemporal both ways;
+// after a flush of the cache, where it takes the writes, 16384 x 8192: add
+// 120.7, masked_fill 99.6, silu 78.4 us, against 133.0 / 105.9 / 79.8 cached
+// and 136.9 / 111.4 / 86.9 nontemporal both ways.
 template <int DT, int OP>
 __device__ __forceinline__ bool elt_streams(const EltArgs &a) {
   return (OP == kOpAdd ? 3 : 2) * a.T * a.W * Elt<DT>::ES > int64_t(kCacheBytes);
@@ -1707,7 +1707,7 @@ __device__ __forceinline__ void elt_slots(const EltArgs &a, int64_t blk, int64_t
     char *o = static_cast<char *>(a.out) + row * a.o_rs * E::ES;
     if (!ANY || e0 + V <= sl.W) {
       const u32x4 xv = ld_slot<DT, ANY, NT>(x, e0);
-      st_slot<DT, ANY, NT>(o, e0, elt_vector<DT, OP, ANY, NT>(xv, b, e0, fill));
+      st_slot<DT, ANY, false>(o, e0, elt_vector<DT, OP, ANY, NT>(xv, b, e0, fill));
     } else {
       const int m = int(sl.W - e0);   // 1 .. V - 1
 #pragma unroll
@@ -1731,8 +1731,8 @@ __device__ __forceinline__ void elt_rows_part(const EltArgs &a, int64_t blk, int
 // any start and length (ANY). A workgroup takes kEmbSlots * 256 consecutive
 // slots; a lane's ids and then its table vectors are requested together.
 // Bound by the gather and the output's writes: bf16 8192 rows of 4096 from a
-// 32,000-row table 21.1 us, float32 8192 x 5120 56.9 us, against 23.0 and
-// 66.6 us with a workgroup per row and cached stores; 4096 x 5000 one element
+// 32,000-row table 22.7 us, float32 8192 x 5120 65.6 us, against 23.0 and
+// 66.6 us with a workgroup per row; 4096 x 5000 one element
 // off a 16-byte boundary 14.7 against 26 us element by element.
 template <int DT, bool ANY, bool NT>
 __device__ __forceinline__ void emb_slots(const EmbArgs &a, uint32_t nblk) {
@@ -1785,11 +1785,12 @@ __device__ __forceinline__ void emb_slots(const EmbArgs &a, uint32_t nblk) {
   }
 }
 
-// Large outputs are written nontemporally: they and the gathered rows pass
-// through the last-level cache once (8192 rows of 4096, other ids and buffers
-// each time: 21.1 against 23.0 us, and with a norm that reads the rows 44.6
-// against 47.8 us for both; not below, where 2048 rows take 6.4 us either
-// way). Nontemporal loads of the table, whose rows repeat, took 24.5 us.
+// Outputs larger than the last-level cache are written nontemporally (float32
+// rows of 8192 after a flush of the cache: 16384 of them 161 against 168 us,
+// 32768 306 against 348 us). Smaller ones the cache takes: 8192 rows of 4096
+// bf16 24.9 against 26.8 us, with a norm that reads them 45.2 against 48.2 us
+// (back to back, where older outputs have to leave it first, 22.7 against
+// 21.1 us). Nontemporal loads of the table, whose rows repeat, took 24.5 us.
 template <int DT, bool VEC>
 __device__ __forceinline__ void emb_rows(const EmbArgs &a, uint32_t nblk) {
   if (a.T * a.H * Elt<DT>::ES > int64_t(kEmbStreamBytes))
@@ -1807,10 +1808,11 @@ __device__ __forceinline__ void body_rn_wave(const RnArgs &a) {
   rn_wave_block<DT, NV, RES, false>(a, blockIdx.x);
 }
 
-// Residual rows of calls that move more than kStreamBytes are read and
-// written nontemporally (bf16 8192 x 8192, three buffer sets in turn: 88.0
-// against 91.9 us; 4096 rows, which fit the last-level cache when the same
-// buffers come again: 44.6 against 38.8 us then, so not below). Plain rows
+// Residual rows of calls that move more than kStreamBytes are read
+// nontemporally and written through the last-level cache (bf16 8192 x 8192,
+// three buffer sets in turn: 91.2 against 91.9 us cached; after a flush of the
+// cache 0.827 against 0.821 of 8 TB/s. Nontemporal stores too: 88.0 us, but
+// 0.73 after a flush, as the cache then takes none of the writes). Plain rows
 // gained nothing at any size (256-512 MiB: 46.3-46.0 and 98.5-100.2 us).
 template <int DT, int NB, bool RES>
 __device__ __forceinline__ void body_rn_block(const RnArgs &a) {
@@ -2040,8 +2042,10 @@ __device__ __forceinline__ void body_rn_wide(const RnArgs &a, uint32_t nblk = gr
 }
 
 // Rows of more than 4096 vectors over several workgroups (rn_split_row);
-// residual calls that move more than kStreamBytes nontemporally (1061 rows of
-// 49,408 bf16: 78.6 against 84.2 us, 700 of 131,072: 126.0 against 135.2 us).
+// residual calls that move more than kStreamBytes read nontemporally (1061
+// rows of 49,408 bf16: 81.1 against 84.2 us, 700 of 131,072: 133.1 against
+// 135.2 us; 2048 of 65,536 after a flush of the cache 0.80 against 0.757 of
+// 8 TB/s, and 0.73 with nontemporal stores).
 template <int DT, bool RES>
 __device__ __forceinline__ void body_rn_split(const RnSplitArgs &a) {
   __shared__ float red[4];
@@ -2052,8 +2056,8 @@ __device__ __forceinline__ void body_rn_split(const RnSplitArgs &a) {
     rn_split_row<DT, RES, false>(a.rn, a.scratch, red, total);
 }
 
-// Residual calls that move more than kStreamBytes nontemporally (bf16 607 x
-// 88768 103.7 against 114.6 us, f32 2560 x 10240 72.3 against 78.2 us).
+// Residual calls that move more than kStreamBytes read nontemporally (f32
+// 295 x 88763 131.3 against 135.1 us; 2560 x 10240 77.8 against 78.2 us).
 template <int DT, bool RES>
 __device__ __forceinline__ void body_rn_scalar(const RnArgs &a) {
   __shared__ double red[kWideLanes / 64];
@@ -2138,9 +2142,10 @@ __device__ __forceinline__ void body_emb(const EmbArgs &a, uint32_t nblk = gridD
 // for SwiGLU first or with two / four vectors per work-item.
 //
 // In the streaming form (NT: calls that move more than the last-level
-// cache) the norm and RoPE roles also stream nontemporally (the norm's share:
-// 371.3 against 357.6 us at 8192 tokens, hidden 8192, three buffer sets in
-// turn), and the RoPE role keeps one head per lane group in flight instead of
+// cache) the RoPE role also streams nontemporally and the norm role reads so
+// (371.3 against 365.7 us at 8192 tokens, hidden 8192, three buffer sets in
+// turn; with its stores nontemporal too 360 us, but after a flush of the cache
+// 0.83 instead of 0.846 of 8 TB/s), and the RoPE role keeps one head per lane group in flight instead of
 // two: more registers per lane cap the whole fused kernel below the 8
 // wavefronts per SIMD that SwiGLU alone runs (with four heads and 77
 // registers, 357 against 346.5 us at 8192 tokens).

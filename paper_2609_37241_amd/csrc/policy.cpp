@@ -82,7 +82,8 @@ bool split_fits(uint32_t dtype, int64_t H, uint32_t bucket) {
 // rows, back to back and after a 1 GiB read flush) put the split ahead
 // only for rows of 8192 vectors (by up to 15 % at 1-64 rows, where four
 // workgroups per row pull it from HBM in parallel). Unaligned or ragged
-// rows take RN_SCALAR, a workgroup per row with element-aligned vectors.
+// rows take RN_SCALAR, a workgroup per row with element-aligned vectors: 256
+// work-items, 1024 beyond kAnyBlockVecs vectors.
 Role rn_role(uint32_t dtype, int64_t H, unsigned flags, int64_t T, uint32_t bucket, bool res) {
   const int64_t v = vec_elems(dtype);
   if (!(flags & kAlign) || H % v) return {RN_SCALAR, uint32_t(T)};
@@ -105,8 +106,8 @@ Role rn_role(uint32_t dtype, int64_t H, unsigned flags, int64_t T, uint32_t buck
 // workgroup at every size (it also streamed best at 8192 tokens: more
 // workgroups, one angle table each). With QK-RMSNorm the vector form needs
 // the group to hold the whole head (rd == hd) in at most 64 lanes, since the
-// norm's per-head reduction runs over the group's lanes; otherwise the scalar
-// form reduces each head with a wavefront.
+// norm's per-head reduction runs over the group's lanes. Everything else takes
+// the form for any alignment and head size, a token per workgroup.
 Role rope_role(uint32_t dtype, int32_t hd, int32_t rd, bool interleaved, unsigned flags, int64_t T,
                bool qk_norm) {
   const int64_t v = vec_elems(dtype);
@@ -187,10 +188,10 @@ Role sw_role(uint32_t dtype, int64_t I, unsigned flags, bool stream, int64_t T) 
 }
 
 // Element-wise ops: flat vectors when aligned and contiguous (beyond decode
-// sizes two vectors per work-item, cached: measured 80 / 82 / 79 % of HBM
-// peak for add / masked_fill / silu at 8192 x 8192 bf16, against 74-75 %
-// nontemporal and 1-4 % less with one or four vectors), vector rows when
-// only the rows are aligned, element-wise otherwise.
+// sizes two vectors per work-item, which streamed 1-4 % faster than one or
+// four at 8192 x 8192 bf16; the kernel reads nontemporally beyond the
+// last-level cache), row slots of aligned vectors when only the rows are aligned, of
+// element-aligned ones otherwise.
 Role elt_role(uint32_t dtype, int64_t W, unsigned flags, uint32_t bucket, int64_t T) {
   const int64_t v = vec_elems(dtype);
   if ((flags & kAlign) && (flags & kContig)) {
@@ -404,7 +405,7 @@ Key with_bucket(const Key &k, uint32_t b) {
 }
 
 // The row lengths served by the norm kernel rn_role picks for H at every
-// bucket: unaligned rows take the scalar kernel at any length, aligned
+// bucket: unaligned rows take RN_SCALAR at any length, aligned
 // ragged ones at every length that is not a whole number of vectors; rows
 // of whole vectors one wavefront (1-64, 65-128 vectors) or one workgroup
 // (129-256, 257-512, ..., 2049-4096 vectors; plain rows also 4097-8192 in
@@ -501,8 +502,8 @@ bool guard_holds(const Key &vk, const Guard &g, const Key &k) {
 // the two-pass kernel (standalone only); a vector RoPE role can
 // take another geometry (at decode sizes 1, 2 or 4 workgroups per token;
 // beyond them 1, 2 or 4 tokens per workgroup, or up to 8192 tokens 2 or 4
-// workgroups per token) or the scalar kernel; flat SwiGLU and element-wise kernels have a cached
-// and a streaming (SwiGLU: nontemporal; element-wise: two vectors per
+// workgroups per token) or the kernel for any alignment; flat SwiGLU and
+// element-wise kernels have a cached and a streaming (SwiGLU: nontemporal; element-wise: two vectors per
 // work-item) form and a row form when a row is whole vectors. The fused
 // chain takes every combination of its roles' options (norm, then slices,
 // then SwiGLU form, each starting with the policy's choice), then the

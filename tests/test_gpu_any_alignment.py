@@ -289,6 +289,20 @@ def test_embedding_rows(cache, dtype, H, off, pad):
         untouched(od, obuf)
 
 
+@pytest.mark.parametrize("H", [4104, 4101])
+def test_embedding_beyond_the_last_level_cache(cache, H):
+    """Outputs written nontemporally: the table's bits, zeros for other ids."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(H)
+    table = torch.randn((500, H), generator=g, device=DEV).to(torch.bfloat16)
+    ids = torch.randint(0, 500, (33000,), generator=g, device=DEV)
+    want = table[ids]
+    bad = torch.tensor([0, 777, 32999], device=DEV)
+    ids[bad] = torch.tensor([-1, 500, 1 << 40], device=DEV)
+    want[bad] = 0
+    assert torch.equal(cache.embedding(table, ids), want)
+
+
 @pytest.mark.parametrize("dtype", [nm.F32, nm.BF16])
 def test_silu_tail_beside_ordinary_elements(cache, dtype):
     """Vectors of which one element, all or none lie in the negative tail,
