@@ -944,7 +944,10 @@ __device__ __forceinline__ float rot_b(float x, float y, float c, float s) {
 // heads requested where a group has one, some 250 instructions preceded the
 // last load. 8 one-token chains 18.9 -> 16.9 us, 32 captured 8-token chains
 // 96.9 -> 90.0 us, the 512-token GQA chain 12.3 -> 11.8 us. Two heads at a time
-// beyond decode sizes: four cost 107 instead of 69 registers a lane. Several
+// beyond decode sizes: four cost 107 instead of 69 registers a lane. With the
+// QK norm one: two cost 90-110 instead of 75-83, and at decode sizes a group
+// has one (eight 48-token chains 33.7 -> 32.7 us; 2048 tokens alone
+// 9.98 -> 9.61 us, 8192 tokens after a flush 0.74 -> 0.765 of 8 TB/s). Several
 // tokens are spread over all groups: with the second token's heads left to
 // the first one's groups, four 308-token chains of 16 heads took 24.6 us, now
 // 23.5, and 8192 tokens of 9 heads with their norm and SwiGLU 130.4, now 122.7.
@@ -2071,7 +2074,7 @@ __device__ __forceinline__ void body_rn_scalar(const RnArgs &a) {
 template <int DT, bool QKN, bool INTER>
 __device__ __forceinline__ void body_rope_vec(const RopeArgs &a) {
   __shared__ float lds[2 * 256 * kRopeTokensMax];
-  rope_vec_block<DT, false, 2, QKN, INTER>(a, blockIdx.x, lds);
+  rope_vec_block<DT, false, QKN ? 1 : 2, QKN, INTER>(a, blockIdx.x, lds);
 }
 
 template <int DT, bool QKN>
@@ -2146,7 +2149,7 @@ __device__ __forceinline__ void body_emb(const EmbArgs &a, uint32_t nblk = gridD
 // (371.3 against 365.7 us at 8192 tokens, hidden 8192, three buffer sets in
 // turn; with its stores nontemporal too 360 us, but after a flush of the cache
 // 0.83 instead of 0.846 of 8 TB/s), and the RoPE role keeps one head per lane group in flight instead of
-// two: more registers per lane cap the whole fused kernel below the 8
+// two (as with the QK norm at any size): more registers per lane cap the whole fused kernel below the 8
 // wavefronts per SIMD that SwiGLU alone runs (with four heads and 77
 // registers, 357 against 346.5 us at 8192 tokens).
 template <int DT, bool WAVE, int N, bool NT>
@@ -2171,7 +2174,7 @@ __device__ __forceinline__ void body_chain(const ChainArgs &a, uint32_t nblk) {
   if (b < R) {
     chain_norm_role<DT, WAVE, N, NT>(a, b);
   } else if (b < R + P) {
-    rope_vec_block<DT, NT, NT ? 1 : 2, QKN, INTER>(a.rope, b - R, lds);
+    rope_vec_block<DT, NT, NT || QKN ? 1 : 2, QKN, INTER>(a.rope, b - R, lds);
   } else {
     sw_flat_part<DT, 1, NT>(a.sw, b - R - P, S);
   }

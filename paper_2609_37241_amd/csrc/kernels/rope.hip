@@ -1,6 +1,6 @@
 // RoPE-on-Q-and-K kernels (in place), with and without the per-head QK
 // RMSNorm, rotate-half or GPT-J pairs, one per install-policy variant and
-// dtype (the scalar kernels take the pairing, position width and angle
+// dtype (the any-alignment kernels take the pairing, position width and angle
 // source at run time), each also without kernel arguments (its block read
 // from this device's resident table).
 #include "../internal.h"
@@ -11,7 +11,7 @@ using namespace dev;
 
 // QKN: per-head RMSNorm of Q and K before the rotation; INTER: GPT-J pairs.
 template <int DT, bool QKN, bool INTER>
-__global__ __launch_bounds__(256) void k_rope_vec(RopeArgs a) {
+__global__ __launch_bounds__(256, QKN ? 6 : 1) void k_rope_vec(RopeArgs a) {
   body_rope_vec<DT, QKN, INTER>(a);
 }
 
@@ -27,7 +27,7 @@ __global__ __launch_bounds__(256) void k_rope_scalar(RopeArgs a) {
 __device__ __align__(256) ResidentBlock resident_rope[2 * kResidentSlots];
 
 template <int DT, bool QKN, bool INTER>
-__global__ __launch_bounds__(256) void k_rope_vec_res() {
+__global__ __launch_bounds__(256, QKN ? 6 : 1) void k_rope_vec_res() {
   RopeArgs a;
   uint32_t g;
   if (resident_args(resident_rope + DT * kResidentSlots, a, g)) body_rope_vec<DT, QKN, INTER>(a);
