@@ -241,17 +241,20 @@ __device__ inline void add_squares(double *acc, const float *f) {
   for (int e = 0; e < N; ++e) acc[e & 1] = __builtin_fma(double(f[e]), double(f[e]), acc[e & 1]);
 }
 
-// RN_f32(1 / sqrt(m)) for m = ss / H + eps, up to the last bit of the double
-// before rounding: the hardware's reciprocal square root and one Newton step
-// (v_rsq_f64 is good to 2^-24, the step squares that) instead of a
+// RN_f32(1 / sqrt(m)) for m = ss / H + eps: the hardware's reciprocal square
+// root and two Newton steps (v_rsq_f64 is good to 2^-24; a step squares that
+// and takes half as much again: one step alone would leave 2^-47) instead of a
 // division, a square root and another division, about 100 dependent float64
-// instructions between a row's sum and its first store. 0 and infinity, where
-// the step has 0 * infinity in it, keep the first value.
+// instructions between a row's sum and its first store. Before the rounding to
+// float32 the error is at most 2.5 * 2^-53, as theirs: 1 / H, its product with
+// ss and the last step's product and sum. 0 and infinity, where a step has
+// 0 * infinity in it, keep the first value.
 __device__ inline float inv_rms(double ss, double rcp_h, float eps) {
   const double m = __builtin_fma(ss, rcp_h, double(eps));
   const double y = __builtin_amdgcn_rsq(m);
-  const double e = __builtin_fma(-m * y, y, 1.0);
-  const double r = __builtin_fma(0.5 * y, e, y);
+  double r = y;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) r = __builtin_fma(0.5 * r, __builtin_fma(-m * r, r, 1.0), r);
   return float(__builtin_isfinite(r) ? r : y);
 }
 

@@ -3,6 +3,9 @@ length, at the edges of their register and vector layouts: operands at
 different distances from a 16-byte boundary, odd row strides, lengths just
 below, at and above a whole number of vectors or of workgroups. Expected
 values from the oracle, tolerances of tests/parity.py."""
+from fractions import Fraction
+from math import isqrt
+
 import numpy as np
 import pytest
 import torch
@@ -229,6 +232,51 @@ def test_many_short_norm_rows(cache, dtype, vecs, tail, res):
     check("y", host(yd), wy, dtype)
     check("y of 2048 rows", host(few), wy[1:], dtype)
     untouched(yd, ybuf)
+
+
+def _near_tie_row(r, H):
+    """Seven float32 values, 0.5 first, whose sum of squares S puts sqrt(H / S)
+    between 2^-51 and 2^-49.5 (relative) from the midpoint of two adjacent
+    float32 numbers, and the one it rounds to. The squares are whole multiples
+    of 2^-52 and S < 2, so that any order of float64 sums is exact."""
+    while True:
+        lo = np.float32(np.sqrt(H / r.uniform(1.05, 1.2)))
+        hi = np.nextafter(lo, np.float32(np.inf))
+        tie = (Fraction(float(lo)) + Fraction(float(hi))) / 2
+        at = H / tie ** 2                              # the sum of squares at the midpoint
+        shift = 1 - Fraction(float(r.choice([-1, 1]) * 2.0 ** r.uniform(-50.5, -48.5)))
+        left = int(at * shift * 2 ** 52) - 2 ** 50
+        n = [isqrt(left) // 4 * 4]                     # 24 bits of mantissa
+        left -= n[0] ** 2
+        while len(n) < 6:
+            n.append(isqrt(left))
+            left -= n[-1] ** 2
+        total = Fraction(2 ** 50 + sum(i * i for i in n), 2 ** 52)
+        off = (at / total - 1) / 2                     # of sqrt(H / S) above the tie, relative
+        if 2.0 ** -51 <= abs(off) <= 2.0 ** -49.5:
+            return [0.5] + [i * 2.0 ** -26 for i in n], hi if off > 0 else lo
+
+
+@pytest.mark.parametrize("res", [False, True], ids=["rmsnorm", "residual"])
+@pytest.mark.parametrize("T,H", [(2000, 7), (3000, 1139), (1500, 4099), (1000, 8203), (500, 36873)])
+def test_norm_scale_keeps_the_precision_of_float64(cache, T, H, res):
+    """The scale 1 / sqrt(S / H) rounds to the nearest float32 down to 2^-51
+    from a tie: a division, a square root and another division in float64 (or
+    a reciprocal, a product and a refined reciprocal square root) are good to
+    2.5 * 2^-53 < 2^-51, a scale with fewer bits is not. A wavefront per row, 256
+    and 1024 work-items per row, and rows held in part."""
+    r = rng(H)
+    x, want = np.zeros((T, H), np.float32), np.empty(T, np.float32)
+    for i in range(T):
+        row, want[i] = _near_tie_row(r, H)
+        x[i, :7] = row
+    xd = torch.from_numpy(x).to(DEV)
+    w = torch.ones(H, device=DEV)
+    y = cache.residual_rmsnorm(xd, torch.zeros_like(xd), w, 0.0)[0] if res else \
+        cache.rmsnorm(xd, w, 0.0)
+    got = 2 * host(y[:, 0].contiguous())               # y = (0.5 * scale) * 1, exactly
+    wrong = int((got != want).sum())
+    assert wrong == 0
 
 
 @pytest.mark.parametrize("op,dtype,T,W,pad", [
