@@ -11,20 +11,32 @@ using namespace dev;
 
 // RNV: RN_WAVE_1/2 (one wavefront per row) or RN_BLOCK_1..16 (one
 // workgroup per row); SWV: SW_FLAT or SW_FLAT_NT; QKN: QK norm before the
-// rotation; INTER: GPT-J pairs. The streaming form with the QK norm is held to
-// six wavefronts per SIMD (75 registers instead of 83, no spills; seven
-// spill): its RoPE role has one head in flight per work-item, so the loads
-// in flight are the wavefronts'. bf16 8192 tokens of 32 + 8 heads 166.4 against
-// 168.4 us back to back, 72 heads 0.849 against 0.833 of 8 TB/s after a flush.
+// rotation; INTER: GPT-J pairs.
+//
+// Eight wavefronts per SIMD hide the most memory latency in the streaming
+// forms. With the QK norm they are held to that (no spills; 61 registers a lane
+// in bf16, 58 in float32), and the compiler loads their arguments where they are
+// used, as in bf16 with a workgroup per norm row: chain_args has all of them in
+// scalar registers at once, 105, which leaves seven wavefronts. After a flush
+// of the cache, against chain_args: bf16 8192 tokens of 72 heads 341.0 and 344.3
+// us, of 9 heads 111.8 and 113.0; 72 heads with the QK norm (then six wavefronts)
+// 345.2 and 347.7. The other streaming forms gain more from the one round trip
+// of chain_args (back to back, bf16 rows of 512 elements 114.8 against 117.5 us,
+// float32 rows of 4096 162.0 against 163.6).
 template <int DT, int RNV, int SWV, bool QKN, bool INTER>
-__global__ __launch_bounds__(256, QKN && SWV == SW_FLAT_NT && RNV <= RN_BLOCK_4 ? 6 : 1)
-void k_chain(ChainArgs) {
+__global__ __launch_bounds__(256, QKN && SWV == SW_FLAT_NT && RNV <= RN_BLOCK_4 ? 8 : 1)
+void k_chain(ChainArgs a) {
   constexpr bool wave = RNV <= RN_WAVE_2;
   constexpr int n = wave ? 1 << (RNV - RN_WAVE_1) : 1 << (RNV - RN_BLOCK_1);
-  ChainArgs c;
-  uint32_t g;
-  chain_args(c, g);
-  body_chain<DT, wave, n, SWV == SW_FLAT_NT, QKN, INTER>(c, g);
+  constexpr bool nt = SWV == SW_FLAT_NT;
+  if constexpr (nt && (QKN || (DT == kBF16 && !wave))) {
+    body_chain<DT, wave, n, nt, QKN, INTER>(a, gridDim.x);
+  } else {
+    ChainArgs c;
+    uint32_t g;
+    chain_args(c, g);
+    body_chain<DT, wave, n, nt, QKN, INTER>(c, g);
+  }
 }
 
 // Resident argument blocks of this dtype's fused chain: one table per GPU,

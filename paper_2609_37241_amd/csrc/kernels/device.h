@@ -950,8 +950,10 @@ __device__ __forceinline__ float rot_b(float x, float y, float c, float s) {
 // beyond decode sizes: four cost 107 instead of 69 registers a lane. With the
 // QK norm one: two cost 90-110 instead of 75-83, and at decode sizes a group
 // has one (eight 48-token chains 33.7 -> 32.7 us; 2048 tokens alone
-// 9.98 -> 9.61 us, 8192 tokens after a flush 0.74 -> 0.765 of 8 TB/s). Several
-// tokens are spread over all groups: with the second token's heads left to
+// 9.98 -> 9.61 us, 8192 tokens after a flush 0.74 -> 0.765 of 8 TB/s); the
+// streaming form, which has wavefronts enough to cover their latency, asks for
+// the weights after the reduction: 61 registers and eight wavefronts per SIMD
+// instead of 75 and six. Several tokens are spread over all groups: with the second token's heads left to
 // the first one's groups, four 308-token chains of 16 heads took 24.6 us, now
 // 23.5, and 8192 tokens of 9 heads with their norm and SwiGLU 130.4, now 122.7.
 template <int DT, bool NT, int PF, bool QKN, bool INTER, bool MULTI>
@@ -995,6 +997,11 @@ __device__ __forceinline__ void rope_tokens_block(const RopeArgs &a, int64_t t, 
     return b;
   };
   u32x4 x1[PF], x2[PF], w1[QKN ? PF : 1], w2[QKN ? PF : 1];
+  auto weights = [&](int j, int h) {   // the head's chunk of the Q or K weights
+    const char *w = static_cast<const char *>(h < a.nq ? a.qw : a.kw) + cbytes;
+    w1[j] = *reinterpret_cast<const u32x4 *>(w);
+    if constexpr (!INTER) w2[j] = *reinterpret_cast<const u32x4 *>(w + off2);
+  };
   auto gather = [&](int h0) {
 #pragma unroll
     for (int j = 0; j < PF; ++j) {
@@ -1004,11 +1011,7 @@ __device__ __forceinline__ void rope_tokens_block(const RopeArgs &a, int64_t t, 
         const char *b = head(tt, i - tt * nh);
         x1[j] = ld16<NT>(reinterpret_cast<const u32x4 *>(b));
         if constexpr (!INTER) x2[j] = ld16<NT>(reinterpret_cast<const u32x4 *>(b + off2));
-        if constexpr (QKN) {   // the head's chunk of the Q or K weights
-          const char *w = static_cast<const char *>(i - tt * nh < a.nq ? a.qw : a.kw) + cbytes;
-          w1[j] = *reinterpret_cast<const u32x4 *>(w);
-          if constexpr (!INTER) w2[j] = *reinterpret_cast<const u32x4 *>(w + off2);
-        }
+        if constexpr (QKN && !NT) weights(j, i - tt * nh);
       }
     }
   };
@@ -1050,6 +1053,7 @@ __device__ __forceinline__ void rope_tokens_block(const RopeArgs &a, int64_t t, 
         }
         ss = group_sum(ss, cpb);
         const float inv = rsqrtf(ss / float(a.hd) + a.eps);
+        if constexpr (NT) weights(j, h);
         float w[V];
         E::unpack(w1[j], w);
 #pragma unroll
