@@ -263,10 +263,10 @@ __device__ inline float inv_rms(double ss, double rcp_h, float eps) {
 // k < NV. With RES, h = RN(x + r) is written to res_out and normalised.
 // LANES = 64: one wavefront per row, no barrier. LANES = 256 or kWideLanes:
 // one workgroup of that many work-items.
-// Without NT (decode sizes) the weight vectors are requested together with the
-// row, so the row costs one memory round trip; with NT (streaming sizes) they
+// Without LATE (decode sizes) the weight vectors are requested together with the
+// row, so the row costs one memory round trip; with it (streaming sizes) they
 // are loaded after the reduction to keep fewer registers live.
-template <int DT, int NV, bool RES, int LANES, bool NT>
+template <int DT, int NV, bool RES, int LANES, bool NT, bool LATE = NT>
 __device__ __forceinline__ void rn_row_regs(const RnArgs &a, int64_t row, int lane, float *red) {
   using E = Elt<DT>;
   constexpr int V = E::V;
@@ -290,8 +290,8 @@ __device__ __forceinline__ void rn_row_regs(const RnArgs &a, int64_t row, int la
       rv[k] = vi < nvec ? ld16<NT>(rr + vi) : u32x4{0, 0, 0, 0};
     }
   }
-  u32x4 wv[NT ? 1 : NV];
-  if constexpr (!NT) {
+  u32x4 wv[LATE ? 1 : NV];
+  if constexpr (!LATE) {
 #pragma unroll
     for (int k = 0; k < NV; ++k) {
       const int vi = lane + LANES * k;
@@ -334,7 +334,7 @@ __device__ __forceinline__ void rn_row_regs(const RnArgs &a, int64_t row, int la
     if (vi < nvec) {
       float f[V], w[V];
       E::unpack(xv[k], f);
-      if constexpr (NT)
+      if constexpr (LATE)
         E::unpack(wr[vi], w);
       else
         E::unpack(wv[k], w);
@@ -1823,13 +1823,18 @@ __device__ __forceinline__ void body_rn_wave(const RnArgs &a) {
 // three buffer sets in turn: 91.2 against 91.9 us cached; after a flush of the
 // cache 0.827 against 0.821 of 8 TB/s. Nontemporal stores too: 88.0 us, but
 // 0.73 after a flush, as the cache then takes none of the writes). Plain rows
-// gained nothing at any size (256-512 MiB: 46.3-46.0 and 98.5-100.2 us).
+// gained nothing at any size (256-512 MiB: 46.3-46.0 and 98.5-100.2 us). With
+// eight or more vectors a work-item, whose registers leave two to four
+// wavefronts per SIMD either way, the weights are requested with the row: asked
+// for after the reduction nothing covers them (float32 2048 x 16384 after a
+// flush 83.6 against 93.7 us, 86.7 cached; back to back 83.8 against 91.9 and
+// 103.3; bf16 2730 x 24,576 84.8 against 92.8 and 86.4, 84.8 against 92.4 and 101.5).
 template <int DT, int NB, bool RES>
 __device__ __forceinline__ void body_rn_block(const RnArgs &a) {
   __shared__ float red[4];
   if constexpr (RES) {
     if (4 * a.T * a.H * Elt<DT>::ES > int64_t(kStreamBytes)) {
-      rn_row_regs<DT, NB, RES, 256, true>(a, blockIdx.x, threadIdx.x, red);
+      rn_row_regs<DT, NB, RES, 256, true, (NB < 8)>(a, blockIdx.x, threadIdx.x, red);
       return;
     }
   }

@@ -283,6 +283,8 @@ def test_norm_scale_keeps_the_precision_of_float64(cache, T, H, res):
     ("add", nm.BF16, 4500, 10007, 0), ("add", nm.F32, 2000, 12000, 0),
     ("silu", nm.BF16, 8200, 8200, 8), ("masked_fill", nm.BF16, 9000, 8000, 0),
     ("residual", nm.BF16, 6000, 8192, 0), ("residual", nm.F32, 6000, 4100, 4),
+    # eight and sixteen vectors a work-item
+    ("residual", nm.BF16, 3000, 16384, 0), ("residual", nm.F32, 2500, 10252, 4),
     # split over 3 and 9 workgroups: slices of 1408 and of 2048 vectors, the last shorter
     ("residual", nm.BF16, 1500, 32776, 8), ("residual", nm.F32, 400, 65540, 0),
     # ragged: 256 and 1024 work-items a row, and rows held in part
