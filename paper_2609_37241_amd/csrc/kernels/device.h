@@ -189,7 +189,8 @@ __device__ inline double wave_sum(double v) {
 // Sum over aligned groups of n consecutive lanes (n a power of two, at most
 // 64, the same for the whole wavefront); every lane of a group returns the
 // same, bitwise equal sum. Lanes of one group must be active together.
-__device__ inline float group_sum(float v, int n) {
+template <typename T>
+__device__ inline T group_sum(T v, int n) {
   if (n >= 2) v += dpp_mov<0xB1>(v);    // lane ^ 1
   if (n >= 4) v += dpp_mov<0x4E>(v);    // lane ^ 2
   if (n >= 8) v += dpp_mov<0x141>(v);   // the other quad of the half row
@@ -1184,6 +1185,14 @@ __device__ __forceinline__ void st_part(char *head, int e, int m, const float *f
 // QKN: the group sums the squares of its head, so a group is at most 64
 // lanes; chunks beyond that (float32, INTER, more than 256 elements) and the
 // elements past rd, which are normalised only, are read again after the sum.
+// A group has lanes enough for eight chunks of those each: with the lanes of
+// the rotated chunks only, one lane would take a head of 512 with rd = 8 alone.
+// A lane's squares go to four float32 chains, and the lanes' sums join in
+// float64: no further from the exact sum than a wavefront per head, whose
+// lanes hold at most eight squares each (rms of the relative error of heads
+// of 64-512: 0.42-0.57 of 2^-24 against 0.63-0.72; one float32 chain and a
+// float32 group sum had 0.70-0.80, 2.7 at 512 with rd = 64 and 17 with rd = 8).
+// That costs 2048 tokens of 40 heads of 96 0.2 us of 9.2 (bf16).
 //
 // Bound by memory latency and the lanes that a group leaves idle: 2048
 // tokens of 64 heads of 96 (bf16, six of eight lanes) take 9.7 us (5.3 TB/s),
@@ -1197,7 +1206,9 @@ __device__ __forceinline__ void rope_any_block(const RopeArgs &a, int64_t t, flo
   constexpr int V = E::V;
   const int P2 = a.rd >> 1;
   const int span = INTER ? a.rd : P2;
-  const int cpb = (span + V - 1) / V;
+  const int pass = QKN ? a.hd - a.rd : 0;
+  int cpb = (span + V - 1) / V;
+  if (QKN && pass > 8 * V * cpb) cpb = (pass + 8 * V - 1) / (8 * V);
   int lg = cpb > 1 ? 32 - __builtin_clz(unsigned(cpb - 1)) : 0;
   if (QKN && lg > 6) lg = 6;
   const int G = 1 << lg;
@@ -1206,7 +1217,6 @@ __device__ __forceinline__ void rope_any_block(const RopeArgs &a, int64_t t, flo
   const int nh = a.nq + a.nk;
   const int e0 = lane * V;
   const int m = span - e0;               // elements of this lane's chunk (idle: <= 0)
-  const int pass = QKN ? a.hd - a.rd : 0;
   float *cs = lds, *sn = lds + 256;
 
   // the angle operands of pair threadIdx.x, ahead of the heads
@@ -1310,24 +1320,23 @@ __device__ __forceinline__ void rope_any_block(const RopeArgs &a, int64_t t, flo
       const char *hw = nullptr;
       if constexpr (QKN) {
         hw = weights(h);
-        float ss = 0.0f;
+        float sq[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        auto squares = [&](const float *f) {
 #pragma unroll
-        for (int i = 0; i < V; ++i) ss = __builtin_fmaf(f1[i], f1[i], ss);
-        if constexpr (!INTER) {
-#pragma unroll
-          for (int i = 0; i < V; ++i) ss = __builtin_fmaf(f2[i], f2[i], ss);
-        }
+          for (int i = 0; i < V; ++i) sq[i & 3] = __builtin_fmaf(f[i], f[i], sq[i & 3]);
+        };
+        squares(f1);
+        if constexpr (!INTER) squares(f2);
         auto add = [&](int e, int n) {
           float f[V];
           E::unpack(ld_part<DT>(b, e, n), f);
-#pragma unroll
-          for (int i = 0; i < V; ++i) ss = __builtin_fmaf(f[i], f[i], ss);
+          squares(f);
         };
         if constexpr (INTER)
           for (int e = e0 + G * V; e < span; e += G * V) add(e, span - e);
         for (int e = e0; e < pass; e += G * V) add(a.rd + e, pass - e);
-        ss = group_sum(ss, G);
-        inv = rsqrtf(ss / float(a.hd) + a.eps);
+        const double ss = group_sum(double((sq[0] + sq[1]) + (sq[2] + sq[3])), G);
+        inv = rsqrtf(float(ss) / float(a.hd) + a.eps);
       }
       if (m > 0) {
         rotate(b, e0, m, f1, f2, inv, w1[QKN ? j : 0], w2[QKN ? j : 0]);
