@@ -9,16 +9,19 @@ the missed key and calls again -- the paper's miss path (Sec. 3.5), with
 "compile" replaced by selecting a precompiled kernel variant.
 
 PyTorch is used for device memory and streams only. There is no fallback:
-if libtri.so or _fast.so is missing, importing this package raises.
+if libtri.so is missing, importing this package raises.
 
 The op methods first hand their arguments to the native form of the same
 call (csrc/binding/fast.cpp), which takes plain tensors on the cache's
 device and returns None for everything else; the Python code after it then
-makes the checks, raises the errors and records prepared calls.
+makes the checks, raises the errors and records prepared calls. Without
+_fast.so, or with one built against another torch, the Python code does that
+for every call (some 2-4 us more of host time each), and importing warns.
 """
 from __future__ import annotations
 
 import ctypes as C
+import warnings
 from typing import Optional, Tuple
 
 import torch
@@ -33,11 +36,6 @@ __all__ = ["SpecCache", "Graph", "TriError", "dtype_code", "rope_ext", "Selectio
            "E_NOMEM", "E_LAUNCH", "E_RUNTIME", "F32", "BF16", "AUTO_INSTALL"]
 
 _dll = L.load()
-try:
-    from . import _fast     # after libtri.so, which it shares
-except ImportError as e:
-    raise ImportError("the binding's extension module _fast.so is missing or does not load: "
-                      "build it first (python -c 'import __graft_entry__ as g; g.build()')") from e
 
 
 class TriError(RuntimeError):
@@ -47,7 +45,34 @@ class TriError(RuntimeError):
         super().__init__(f"{what}: {name} ({status})" if what else f"{name} ({status})")
 
 
-_fast.setup(TriError, RopeExt, ChainArgs)
+class _PythonForm:
+    """In the place of a native Handle: every call is left to the Python form."""
+
+    def _decline(self, *args):
+        return None
+
+    rmsnorm = residual_rmsnorm = swiglu = silu = add = masked_fill = embedding = _decline
+    rope = chain = layers = close = _decline
+
+
+def _native_calls():
+    """_fast.so, which shares libtri.so, or None: missing, not loading, or
+    built against another torch than this one, whose tensors it would misread."""
+    try:
+        from . import _fast
+        if _fast.torch_version != torch.__version__:
+            raise ImportError(f"built against torch {_fast.torch_version}, "
+                              f"not {torch.__version__}")
+    except ImportError as e:
+        warnings.warn(f"the binding's extension module _fast.so is not used ({e}); calls take the "
+                      "slower Python form. To build it: python -c 'import __graft_entry__ as g; "
+                      "g.build()'", RuntimeWarning, stacklevel=2)
+        return None
+    _fast.setup(TriError, RopeExt, ChainArgs)
+    return _fast
+
+
+_native = _native_calls()
 
 _DT = {torch.float32: F32, torch.bfloat16: BF16}
 
@@ -250,7 +275,7 @@ class Prepared:
 class SpecCache:
     """One native specialization cache (bound to the current device)."""
 
-    _fast = None      # the native op calls (set with the handle)
+    _fast = _PythonForm()      # the native op calls (set with the handle)
 
     def __init__(self, capacity: int = 0, auto_install: bool = False, jit: bool = False,
                  code_dir: Optional[str] = None, autotune: bool = False,
@@ -274,7 +299,8 @@ class SpecCache:
             raise TriError(st, "tri_spec_cache_create")
         self._h = h
         self._dev = torch.cuda.current_device()   # the device the cache is bound to
-        self._fast = _fast.Handle(h.value, self._dev)
+        if _native is not None:
+            self._fast = _native.Handle(h.value, self._dev)
         self.misses_handled = 0
         self._rec = None                           # prepare(): the recorded entry call
         if code_dir is not None:
@@ -284,8 +310,7 @@ class SpecCache:
 
     def close(self):
         if self._h:
-            if self._fast is not None:
-                self._fast.close()
+            self._fast.close()
             _dll.tri_spec_cache_destroy(self._h)
             self._h = None
 

@@ -10,6 +10,7 @@ from __future__ import annotations
 import concurrent.futures as cf
 import importlib.util
 import os
+import re
 import shutil
 import subprocess
 import sys
@@ -92,21 +93,25 @@ def _obj(src: str) -> str:
     return os.path.join(BUILD, os.path.basename(src) + ".o")
 
 
-def torch_dir() -> str:
-    """The installed torch package's folder, found without importing it."""
-    return importlib.util.find_spec("torch").submodule_search_locations[0]
+def torch_dir() -> Optional[str]:
+    """The installed torch package's folder, found without importing it; None
+    without torch."""
+    spec = importlib.util.find_spec("torch")
+    return spec.submodule_search_locations[0] if spec else None
 
 
-def fast_compile_cmd() -> List[str]:
+def fast_compile_cmd(torch: str) -> List[str]:
     """The binding's native op calls (csrc/binding/fast.cpp) against the
-    installed torch and Python headers."""
-    inc = os.path.join(torch_dir(), "include")
+    headers of the torch in folder `torch` and Python's."""
+    inc = os.path.join(torch, "include")
+    with open(os.path.join(torch, "version.py")) as f:
+        version = re.search(r"__version__ = '([^']+)'", f.read()).group(1)
     src = os.path.join(CSRC, "binding", "fast.cpp")
     system = [inc, os.path.join(inc, "torch", "csrc", "api", "include"),
               os.path.join(ROCM, "include"), sysconfig.get_paths()["include"]]
     flags = [f for d in system for f in ("-isystem", d)]
-    return [CXX, *HOST_FLAGS, "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__", *flags, "-c", src, "-o",
-            _obj(src)]
+    return [CXX, *HOST_FLAGS, "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
+            f'-DTRI_TORCH_VERSION="{version}"', *flags, "-c", src, "-o", _obj(src)]
 
 
 def hip_sources() -> List[str]:
@@ -128,9 +133,11 @@ def build(jobs: Optional[int] = None) -> str:
     src = os.path.join(CSRC, HIP_BACKEND)
     cmds.append([CXX, *HOST_FLAGS, "-D__HIP_PLATFORM_AMD__", "-I", os.path.join(ROCM, "include"),
                  "-c", src, "-o", _obj(src)])
-    fast = fast_compile_cmd()
+    torch = torch_dir()
+    fast = fast_compile_cmd(torch) if torch else None
     with cf.ThreadPoolExecutor(jobs) as ex:
-        for f in [ex.submit(_run, c) for c in [fast, *cmds]]:
+        compiled = ex.submit(_run, fast) if fast else None
+        for f in [ex.submit(_run, c) for c in cmds]:
             f.result()
     objs = [c[-1] for c in cmds]
     rocm_lib = os.path.join(ROCM, "lib")
@@ -139,12 +146,16 @@ def build(jobs: Optional[int] = None) -> str:
           "-Wl,-soname,libtri.so", f"-Wl,-rpath,{rocm_lib}", "-Wl,--no-undefined"])
     shutil.move(tmp, LIB)
     # the binding's extension module: libtri.so beside it, torch's libraries
-    # as the process has loaded them
-    torch_lib = os.path.join(torch_dir(), "lib")
-    tmp = FAST_LIB + ".tmp"
-    _run([CXX, "-shared", "-o", tmp, fast[-1], "-L", PKG, "-ltri", "-L", torch_lib,
-          "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip", "-Wl,-rpath,$ORIGIN"])
-    shutil.move(tmp, FAST_LIB)
+    # as the process has loaded them; libtri.so needs neither and is there by now
+    if fast:
+        compiled.result()
+        tmp = FAST_LIB + ".tmp"
+        _run([CXX, "-shared", "-o", tmp, fast[-1], "-L", PKG, "-ltri", "-L",
+              os.path.join(torch, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip",
+              "-Wl,-rpath,$ORIGIN"])
+        shutil.move(tmp, FAST_LIB)
+    else:
+        print("torch is not installed: libtri.so without the Python binding's extension module")
     # the benchmark's native timing loops, linked against libtri.so
     # and a reference streaming copy (the practical HBM ceiling)
     harness = os.path.join(CSRC, "bench", "harness.cpp")

@@ -522,5 +522,10 @@ PyMODINIT_FUNC PyInit__fast() {
     Py_DECREF(m);
     return nullptr;
   }
+  // what the package compares with the torch it runs on
+  if (PyModule_AddStringConstant(m, "torch_version", TRI_TORCH_VERSION) < 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
   return m;
 }
