@@ -392,14 +392,17 @@ __device__ __forceinline__ void rn_split_row(const RnArgs &a, uint64_t *scratch,
   constexpr int NB = kSplitVecs;
   const int nvec = a.H / V;
   const int S = (nvec + kSplitSpan - 1) / kSplitSpan;
-  const int64_t row = int64_t(blockIdx.x) / S;
-  const int s = int(int64_t(blockIdx.x) - row * S);
+  // both divisions in 32 bits, as the row's first load waits for them (bf16
+  // residual rows: 8 x 40960 6.68 against 6.98 us, 200 x 131,072 48.4 against 48.9)
+  const uint32_t r32 = blockIdx.x / uint32_t(S);
+  const int64_t row = r32;
+  const int s = int(blockIdx.x - r32 * uint32_t(S));
   uint64_t *slots = scratch + kSplitHeaderWords + row * S;
   uint64_t *count = scratch + kSplitHeaderWords + a.T * S + row;
   // equal slices (whole wavefronts of vectors), so that no workgroup of the
   // row only waits for the others (bf16 residual rows of 49,408, whose fourth
   // slice of 2048 vectors would hold 32: 84.2 against 90.1 us at 1061 rows)
-  const int span = ((nvec + S - 1) / S + 63) & ~63;
+  const int span = int(uint32_t(nvec + S - 1) / uint32_t(S) + 63) & ~63;
   const int v0 = s * span + int(threadIdx.x);
   const int vend = (s + 1) * span < nvec ? (s + 1) * span : nvec;
   const u32x4 *xr = reinterpret_cast<const u32x4 *>(static_cast<const char *>(a.x) +
