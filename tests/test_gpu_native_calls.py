@@ -1,8 +1,9 @@
 """The op methods' native form (the binding's extension module) against the
 Python form of the same call, which a torch function mode selects: equal
 results, outputs placed as asked, one miss handled each, the same selection
-record; and the calls that the native form leaves to the Python checks. Each
-case also runs once on a side stream."""
+record, each call served by the form it is meant to test; and the calls that
+the native form leaves to the Python checks. Each case also runs once on a side
+stream."""
 import pytest
 import torch
 from torch.overrides import TorchFunctionMode
@@ -13,6 +14,35 @@ DEV = "cuda:0"
 class PythonForm(TorchFunctionMode):
     def __torch_function__(self, func, types, args=(), kwargs=None):
         return func(*args, **(kwargs or {}))
+
+
+class SideStream:
+    """A stream that is handed over once the inputs are there."""
+
+    def __init__(self):
+        self.s = torch.cuda.Stream()
+
+    @property
+    def cuda_stream(self):
+        torch.cuda.synchronize()
+        return self.s.cuda_stream
+
+
+class Watched:
+    """A cache's native form, and what its calls returned."""
+
+    def __init__(self, cache):
+        self.native, self.returned = cache._fast, []
+
+    def __getattr__(self, name):
+        f = getattr(self.native, name)
+
+        def call(*args):
+            r = f(*args)
+            if name != "close":
+                self.returned.append(r)
+            return r
+        return call
 
 
 def test_native_form_declines_what_is_not_plain():
@@ -66,11 +96,31 @@ def _calls(tri):
         "qk_norm_rope": lambda c, **k: c.qk_norm_rope(t(5, 4, 128), t(5, 2, 128), pos, hw, hw, **k),
         "rope_ext": lambda c, **k: c.rope(t(5, 4, 128), t(5, 2, 128), pos64, ext=ext, **k),
         "empty": lambda c, **k: c.silu(wide[:0], **k),
+        "chain": lambda c, **k: _chains(c, t, pos, (256,), False, **k),
+        "layers": lambda c, **k: _chains(c, t, pos, (256, 520, 1024, 256), True, **k),
     }
 
 
+def _chains(c, t, pos, widths, layers, **k):
+    """Chains of these hidden sizes, as one call of layers or a call each."""
+    args, outs = [], ()
+    for H in widths:
+        q, key = t(5, 4, 128), t(5, 2, 128)
+        a, out = c.chain_args(t(5, H), t(5, H), t(H), q, key, pos, t(5, 688), t(5, 688))
+        args.append(a)
+        outs += (*out, q, key)
+    if layers:
+        c.decode_chain_layers(args, **k)
+    else:
+        for a in args:
+            c.decode_chain_args(a, **k)
+    torch.cuda.synchronize()      # the arguments go with this call
+    return outs
+
+
 NAMES = ["rmsnorm", "rmsnorm_f32_out", "residual", "swiglu", "silu", "add", "masked_fill",
-         "embedding", "rope_qk", "rope_no_k", "qk_norm_rope", "rope_ext", "empty"]
+         "embedding", "rope_qk", "rope_no_k", "qk_norm_rope", "rope_ext", "empty",
+         "chain", "layers"]
 
 
 @pytest.mark.gpu
@@ -79,22 +129,27 @@ def test_native_form_equals_the_python_form(tri, name):
     got = []
     for mode in (None, PythonForm, "stream"):
         call, c = _calls(tri)[name], tri.SpecCache()       # the same draws each time
+        c._fast = watched = Watched(c)
         if mode is PythonForm:
             with PythonForm():
                 r = call(c)
         elif mode == "stream":
-            torch.cuda.synchronize()
-            s = torch.cuda.Stream()
+            s = SideStream()
             r = call(c, stream=s)
-            s.synchronize()
+            s.s.synchronize()
         else:
             r = call(c)
         torch.cuda.synchronize()
         got.append((r if isinstance(r, tuple) else (r,), c.last_selection().as_tuple(), c.stats(),
                     c.misses_handled))
+        if mode is PythonForm:
+            assert watched.returned == [None]
+        else:
+            (r,) = watched.returned
+            assert r is not None and r is not False
         c.close()
     (native, sel, stats, misses), python, side = got
-    assert misses == (0 if name == "empty" else 1)
+    assert misses == {"empty": 0, "layers": 3}.get(name, 1)
     for other in (python, side):
         assert (sel, stats, misses) == other[1:]
         assert len(native) == len(other[0])
@@ -134,7 +189,7 @@ def test_native_form_under_vmap_and_capture(tri):
     form. A call captured into a graph replays on new data."""
     c = tri.SpecCache()
     x = torch.randn(4, 256, device=DEV)
-    with pytest.raises(Exception):
+    with pytest.raises(RuntimeError, match="data pointer"):
         torch.vmap(c.silu)(torch.randn(2, 3, 64, device=DEV))
     y = torch.empty_like(x)
     c.silu(x, out=y)
