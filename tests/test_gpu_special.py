@@ -14,6 +14,7 @@ import torch
 
 from oracle import numerics as nm
 from oracle import ops as O
+from oracle import selection as S
 import workloads as wl
 
 # the oracle meets inf - inf and 0 * inf on purpose here
@@ -118,6 +119,44 @@ def test_norm_zero_row_without_eps_is_nan(cache, dtype):
     check_special("y", host(y), want, dtype)
 
 
+# Rows of any alignment in each of their forms: a workgroup per row, a wavefront
+# per row (more rows than workgroups fit on the chip), 1024 work-items, and
+# two passes; each row starts an element after the end of the last.
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("res", [False, True], ids=["rmsnorm", "residual"])
+@pytest.mark.parametrize("T,vecs", [(9, 30), (9, 700), (2052, 30), (2052, 200), (9, 3000),
+                                    (9, 9000)])
+def test_ragged_norm_special_rows(cache, dtype, T, vecs, res):
+    V = 4 if dtype == nm.F32 else 8
+    H = vecs * V + 3
+    print(f"special: ragged norm {dtype} {T}x{H} residual={res}", flush=True)
+    r = rng(H)
+    x = r.standard_normal((9, H))
+    x[0] = 0.0
+    x[1, H - 1], x[2, 9], x[3, 100] = INF, -INF, NAN
+    x[4] = 1e-30
+    x[5] = 3.0
+    x[6, 5], x[6, H - 2] = 1e4, -1e15
+    x[7] = 1e18                                 # squares finite, their sum too
+    x = np.tile(x, (T // 9, 1))
+    xb, wb = bits(x, dtype), bits(r.uniform(0.5, 1.5, H), dtype)
+    xd, wd = dev(xb, dtype), dev(wb, dtype)
+    for eps in (1e-6, 0.0):                     # without eps the zero row is NaN
+        if res:
+            zero = torch.zeros_like(xd)
+            y, ro = cache.residual_rmsnorm(xd, zero, wd, eps)
+            wy, wh = O.residual_rmsnorm(xb[-9:], bits(np.zeros((9, H)), dtype), wb, eps, dtype)
+            check_special("res_out", host(ro)[-9:], wh, dtype)
+        else:
+            y = cache.rmsnorm(xd, wd, eps)
+            wy = O.rmsnorm(xb[-9:], wb, eps, dtype)
+        torch.cuda.synchronize()
+        assert np.isnan(nm.values(wy, dtype)[0]).all() == (eps == 0.0)
+        check_special("y", host(y)[-9:], wy, dtype)
+        assert torch.equal(y[:9].nan_to_num(nan=7.5), y[-9:].nan_to_num(nan=7.5))
+        assert cache.last_selection().variant == S.RN_SCALAR
+
+
 @pytest.mark.parametrize("dtype", DTYPES)
 def test_swiglu_special_values(cache, dtype):
     print(f"special: swiglu {dtype}", flush=True)
@@ -154,9 +193,10 @@ def test_silu_add_masked_fill_special_values(cache, dtype):
 
 @pytest.mark.parametrize("dtype", DTYPES)
 @pytest.mark.parametrize("qkn", [False, True], ids=["rope", "qk_norm_rope"])
-def test_rope_special_values_and_positions(tri, cache, dtype, qkn):
-    print(f"special: rope {dtype} qkn={qkn}", flush=True)
-    T, nq, nk, hd = 6, 4, 2, 128
+@pytest.mark.parametrize("hd", [128, 90], ids=["aligned", "ragged"])
+def test_rope_special_values_and_positions(tri, cache, dtype, qkn, hd):
+    print(f"special: rope {dtype} qkn={qkn} heads of {hd}", flush=True)
+    T, nq, nk = 6, 4, 2
     r = rng(3)
     q = r.standard_normal((T, nq, hd))
     k = r.standard_normal((T, nk, hd))
@@ -180,6 +220,8 @@ def test_rope_special_values_and_positions(tri, cache, dtype, qkn):
     torch.cuda.synchronize()
     check_special("q", host(qd), wq, dtype)
     check_special("k", host(kd), wkk, dtype)
+    scalar, vec = (S.ROPE_QKN_SCALAR, S.ROPE_QKN_VEC) if qkn else (S.ROPE_SCALAR, S.ROPE_VEC)
+    assert cache.last_selection().variant == (vec if hd == 128 else scalar)
 
 
 def test_embedding_copies_special_rows_bit_for_bit(cache):
