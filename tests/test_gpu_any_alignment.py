@@ -235,6 +235,93 @@ def test_head_norm_sum(cache, hd, rd, inter):
         assert err <= 5.25, err
 
 
+# Rows beyond 2048 vectors, which a workgroup of 1024 takes (four and eight
+# vectors a work-item, two passes), through every way a launch gets its block
+# size: compiled for the row length, without kernel arguments, one version for
+# a range of lengths, and as a chain's norm.
+@pytest.mark.parametrize("path", ["jit", "resident"])
+@pytest.mark.parametrize("res", [False, True], ids=["rmsnorm", "residual"])
+@pytest.mark.parametrize("dtype", [nm.F32, nm.BF16])
+@pytest.mark.parametrize("vecs", [2048, 2049, 4097, 8192, 8193])
+def test_long_rows_compiled_and_resident(cache, dtype, vecs, res, path):
+    import paper_2609_37241_amd as tri
+    H = vecs * (4 if dtype == nm.F32 else 8) + 3
+    r, T = rng(H), 3
+    x, rr = wl.host_array(r, (T, H), dtype), wl.host_array(r, (T, H), dtype)
+    w = wl.host_weight(r, H, dtype)
+    xd, rd, wd = put(x, dtype, 1, 1)[0], put(rr, dtype, 0, 2)[0], wl.to_torch(w, dtype, DEV)
+    other = tri.SpecCache(jit=path == "jit", resident_args=path == "resident")
+    outs = []
+    for c in (cache, other):
+        y, ybuf = put(np.zeros_like(x), dtype, 3, 1)
+        o, obuf = put(np.zeros_like(x), dtype, 2, 0)
+        for _ in range(2):                      # a miss, then a hit
+            y.zero_()
+            if res:
+                c.residual_rmsnorm(xd, rd, wd, 1e-6, out=y, residual_out=o)
+                untouched(o, obuf)
+            else:
+                c.rmsnorm(xd, wd, 1e-6, out=y)
+            untouched(y, ybuf)
+            outs.append((y.clone(), o.clone()))
+    torch.cuda.synchronize()
+    lanes = other.last_selection().launch[0].block_x
+    assert lanes == (1024 if vecs > 2048 else 256)
+    if path == "jit":
+        assert other.version_info(0).jit == 1
+    else:
+        assert other.resident_info()["launches"] == 2
+    other.close()
+    for y, o in outs[1:]:
+        assert torch.equal(y, outs[0][0]) and torch.equal(o, outs[0][1])
+    wy, wh = O.residual_rmsnorm(x, rr, w, 1e-6, dtype) if res else (O.rmsnorm(x, w, 1e-6, dtype), 0)
+    check("y", host(outs[3][0]), wy, dtype)
+    if res:
+        check("res_out", host(outs[3][1]), wh, dtype, exact=True)
+
+
+@pytest.mark.parametrize("resident", [False, True], ids=["arguments", "resident"])
+def test_one_version_for_rows_of_both_block_sizes(resident):
+    import paper_2609_37241_amd as tri
+    c, dtype = tri.SpecCache(generic=True, resident_args=resident), nm.BF16
+    r = rng(3)
+    for H in (16387, 16403, 9, 65555, 16387, 16403, 4099):
+        x, w = wl.host_array(r, (5, H), dtype), wl.host_weight(r, H, dtype)
+        y = c.rmsnorm(put(x, dtype, 1, 0)[0], wl.to_torch(w, dtype, DEV), 1e-6)
+        torch.cuda.synchronize()
+        assert c.last_selection().launch[0].block_x == (1024 if H // 8 > 2048 else 256)
+        check(f"{H}", host(y), O.rmsnorm(x, w, 1e-6, dtype), dtype)
+    assert c.stats()["n_versions"] == 1 and c.stats()["misses"] == 1
+    c.close()
+
+
+@pytest.mark.parametrize("kw", [{}, {"jit": True}, {"resident_args": True}],
+                         ids=["arguments", "jit", "resident"])
+@pytest.mark.parametrize("H", [16387, 16403])
+def test_three_launch_chain_of_long_rows(H, kw):
+    import paper_2609_37241_amd as tri
+    dtype, T, nq, nk, hd, I = nm.BF16, 3, 4, 2, 64, 688
+    r = rng(H)
+    h = dict(x=wl.host_array(r, (T, H), dtype), residual=wl.host_array(r, (T, H), dtype),
+             q=wl.host_array(r, (T, nq, hd), dtype), k=wl.host_array(r, (T, nk, hd), dtype),
+             gate=wl.host_array(r, (T, I), dtype), up=wl.host_array(r, (T, I), dtype),
+             w=wl.host_weight(r, H, dtype), pos=r.integers(0, 99, T).astype(np.int32))
+    want = O.decode_chain(h, 1e-6, 1e4, dtype)
+    c = tri.SpecCache(**kw)
+    for _ in range(2):                          # a miss, then a hit
+        d = {k: put(v, dtype, 1, 0)[0] for k, v in h.items() if k not in ("w", "pos")}
+        y, ro, out = c.decode_chain(d["x"], d["residual"], wl.to_torch(h["w"], dtype, DEV), d["q"],
+                                    d["k"], torch.from_numpy(h["pos"]).to(DEV), d["gate"], d["up"],
+                                    1e-6, 1e4)
+        torch.cuda.synchronize()
+        sel = c.last_selection()
+        assert sel.n_launches == 3 and sel.launch[0].block_x == (1024 if H // 8 > 2048 else 256)
+        for n, g in (("y", y), ("out", out), ("q", d["q"]), ("k", d["k"])):
+            check(n, host(g), want[n], dtype)
+        check("res_out", host(ro), want["res_out"], dtype, exact=True)
+    c.close()
+
+
 @pytest.mark.parametrize("res", [False, True], ids=["rmsnorm", "residual"])
 @pytest.mark.parametrize("dtype", [nm.F32, nm.BF16])
 @pytest.mark.parametrize("vecs,tail", [(0, 3), (64, 0), (64, 1), (128, 3), (129, 0), (256, 2)])
