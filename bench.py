@@ -1000,8 +1000,24 @@ def main():
     emit(args, ce, wall, latency, bandwidth, roofline, cpu)
 
 
+# What the result line leaves to the full record.
+FULL_RECORD_ONLY = {"cache_stats", "resident_blocks", "selection", "qk_norm_decode_selection",
+                    "tuning", "note", "workload", "host_cost_ns", "calls", "versions", "misses"}
+
+
+def brief(x):
+    """A measurement for the result line: medians, five digits."""
+    if isinstance(x, dict):
+        if "median" in x:
+            return brief(x["median"])
+        return {k: brief(v) for k, v in x.items() if k not in FULL_RECORD_ONLY}
+    return float(f"{x:.5g}") if isinstance(x, float) else x
+
+
 def emit(args, ce, wall, latency, bandwidth, roofline, cpu):
-    """Print the one JSON result line."""
+    """Print the one JSON result line, short enough (some 7 kB) to be taken
+    whole from a log, and the full record, with every distribution, on the
+    standard error output."""
     K, W = args.steps, args.warmup
     line = {
         "metric": METRIC, "value": ce["median"], "unit": "µs",
@@ -1027,6 +1043,12 @@ def emit(args, ce, wall, latency, bandwidth, roofline, cpu):
         "cpu_baseline": cpu,
         "paper_context": PAPER_CONTEXT,
     }
+    print(json.dumps(line), file=sys.stderr)
+    line["latency"] = brief(latency)
+    if bandwidth:
+        line["bandwidth_8192"] = {
+            n: {k: brief(v[k]) for k in ("GB/s", "frac_of_matched_ceiling") if k in v}
+            if isinstance(v, dict) else brief(v) for n, v in bandwidth.items()}
     print(json.dumps(line))
 
 
