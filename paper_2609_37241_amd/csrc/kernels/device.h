@@ -4,9 +4,10 @@
 // in both places, so the fused chain computes exactly what the three
 // separate launches compute.
 //
-// Layout conventions: every workgroup has 256 work-items (4 wavefronts of
-// 64). A "vector" is 16 bytes: 4 float32 or 8 bfloat16 elements, loaded and
-// stored with one global_load/store_dwordx4 per lane.
+// Layout conventions: a workgroup has 256 work-items (4 wavefronts of 64),
+// or 1024 for the longest norm rows (kWideLanes). A "vector" is 16 bytes: 4
+// float32 or 8 bfloat16 elements, loaded and stored with one
+// global_load/store_dwordx4 per lane.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -1753,7 +1754,7 @@ __device__ __forceinline__ void elt_rows_part(const EltArgs &a, int64_t blk, int
 // any start and length (ANY). A workgroup takes kEmbSlots * 256 consecutive
 // slots; a lane's ids and then its table vectors are requested together.
 // Bound by the gather and the output's writes: bf16 8192 rows of 4096 from a
-// 32,000-row table 22.7 us, float32 8192 x 5120 65.6 us, against 23.0 and
+// 32,000-row table 22.1-22.7 us, float32 8192 x 5120 65.6 us, against 23.0 and
 // 66.6 us with a workgroup per row; 4096 x 5000 one element
 // off a 16-byte boundary 14.7 against 26 us element by element.
 template <int DT, bool ANY, bool NT>
@@ -1811,7 +1812,7 @@ __device__ __forceinline__ void emb_slots(const EmbArgs &a, uint32_t nblk) {
 // rows of 8192 after a flush of the cache: 16384 of them 161 against 168 us,
 // 32768 306 against 348 us). Smaller ones the cache takes: 8192 rows of 4096
 // bf16 24.9 against 26.8 us, with a norm that reads them 45.2 against 48.2 us
-// (back to back, where older outputs have to leave it first, 22.7 against
+// (back to back, where older outputs have to leave it first, 22.1-22.7 against
 // 21.1 us). Nontemporal loads of the table, whose rows repeat, took 24.5 us.
 template <int DT, bool VEC>
 __device__ __forceinline__ void emb_rows(const EmbArgs &a, uint32_t nblk) {
@@ -2153,6 +2154,16 @@ __device__ __forceinline__ void body_emb(const EmbArgs &a, uint32_t nblk = gridD
   emb_rows<DT, VEC>(a, nblk);
 }
 
+template <int DT, bool WAVE, int N, bool NT>
+__device__ __forceinline__ void chain_norm_role(const ChainArgs &a, uint32_t blk) {
+  if constexpr (WAVE) {
+    rn_wave_block<DT, N, true, NT>(a.rn, blk);
+  } else {
+    __shared__ float red[4];
+    rn_row_regs<DT, N, true, 256, NT>(a.rn, blk, threadIdx.x, red);
+  }
+}
+
 // The fused decode chain: workgroups take the residual-RMSNorm, RoPE-QK and
 // SwiGLU roles by blockIdx range. Norm role: one wavefront per row with N
 // vectors per lane (WAVE) or one workgroup per row with N per work-item;
@@ -2170,22 +2181,12 @@ __device__ __forceinline__ void body_emb(const EmbArgs &a, uint32_t nblk = gridD
 //
 // In the streaming form (NT: calls that move more than the last-level
 // cache) the RoPE role also streams nontemporally and the norm role reads so
-// (371.3 against 365.7 us at 8192 tokens, hidden 8192, three buffer sets in
+// (365.7 against 371.3 us at 8192 tokens, hidden 8192, three buffer sets in
 // turn; with its stores nontemporal too 360 us, but after a flush of the cache
 // 0.83 instead of 0.846 of 8 TB/s), and the RoPE role keeps one head per lane group in flight instead of
 // two (as with the QK norm at any size): more registers per lane cap the whole fused kernel below the 8
 // wavefronts per SIMD that SwiGLU alone runs (with four heads and 77
 // registers, 357 against 346.5 us at 8192 tokens).
-template <int DT, bool WAVE, int N, bool NT>
-__device__ __forceinline__ void chain_norm_role(const ChainArgs &a, uint32_t blk) {
-  if constexpr (WAVE) {
-    rn_wave_block<DT, N, true, NT>(a.rn, blk);
-  } else {
-    __shared__ float red[4];
-    rn_row_regs<DT, N, true, 256, NT>(a.rn, blk, threadIdx.x, red);
-  }
-}
-
 //
 // `nblk` is the launch's workgroup count (gridDim.x, or the resident block's
 // count in a launch without kernel arguments, which must not read gridDim:
